@@ -9,37 +9,6 @@
 namespace smre {
 
 // ---------------------------------------------------------------- checks
-// Order-preserving map of doubles to unsigned 64-bit keys (for atomic max).
-__device__ __forceinline__ unsigned long long dkey(double d) {
-  unsigned long long u = (unsigned long long)__double_as_longlong(d);
-  return (u >> 63) ? ~u : (u | 0x8000000000000000ull);
-}
-__host__ __device__ inline double dkey_inv(unsigned long long k) {
-  unsigned long long u = (k >> 63) ? (k & 0x7FFFFFFFFFFFFFFFull) : ~k;
-  double d;
-  __builtin_memcpy(&d, &u, 8);
-  return d;
-}
-
-// atomicMax of a key that skips the atomic when the stored key is already at
-// least as large (a stale read only costs an unneeded atomic): with many
-// blocks reporting into one address most of them then skip it.
-__device__ __forceinline__ void key_max(unsigned long long* addr, unsigned long long k) {
-  if (k > __hip_atomic_load(addr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(addr, k);
-}
-
-struct Ctrl {
-  int done;            // converged flag read by every sweep kernel
-  int done_sweep;      // sweep at which it converged
-  int nonfinite;       // input check result
-  int abort;           // a sweep kernel's producer/consumer wait gave up
-  unsigned long long delta_key;  // running max |x - prev| of the checked sweep
-  double last_delta;
-  unsigned long long viol_key;   // running max violation
-  unsigned long long icd_sum[4]; // an ICD call's summed work counters
-  unsigned int nf_epoch;         // last ICD call (by its number) whose input was not finite
-};
-
 template <typename TX>
 __device__ __forceinline__ double block_max(double v) {
   __shared__ double red[4];
@@ -313,6 +282,7 @@ __device__ __forceinline__ void ctrl_reset(Ctrl* c) {
   c->delta_key = dkey(0.0);
   c->last_delta = -1.0;
   c->viol_key = dkey(-1.0);
+  c->ticket[0] = c->ticket[1] = c->arrived = c->streamed = 0;
 }
 
 __global__ void ctrl_reset_kernel(Ctrl* c) { ctrl_reset(c); }

@@ -269,6 +269,99 @@ template <int G> __device__ __forceinline__ double group_sum(double v) {
   return v;
 }
 
+// A lane's part of a window's sum of squares; the lane's pixels outside the
+// window (rl / cl: it holds one in the last row / column slot) are set to 0.
+// FP32: two interleaved accumulators (even / odd elements), each with its own
+// compensation when KAHAN, so the dependent add chains are half as long; the
+// corrected partial sums are added at the end.
+template <typename TX, int R, int S, bool KAHAN, int U, int V>
+__device__ __forceinline__ TX lane_sum(TX (&y)[U][V], bool rl, bool cl) {
+  using SS = SideShape<R, S>;
+  TX acc[2] = {0, 0}, comp[2] = {0, 0};
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      TX yv = y[u][v];
+      const bool part_r = (u == U - 1) && (SS::JRL < SS::GR);
+      const bool part_c = (v == V - 1) && (SS::JCL < SS::GC);
+      if (part_r && part_c) yv = (rl && cl) ? yv : TX(0);
+      else if (part_r) yv = rl ? yv : TX(0);
+      else if (part_c) yv = cl ? yv : TX(0);
+      y[u][v] = yv;
+      const int h = (sizeof(TX) == 4) ? ((u * V + v) & 1) : 0;
+      if constexpr (sizeof(TX) == 4 && KAHAN) {
+        if (u * V + v < 2) {
+          // an accumulator's first term: the compensated step from (0, 0)
+          // gives acc = y^2 rounded and comp = 0 exactly (finite y), so
+          // take those values instead of computing y^2 - y^2
+          acc[h] = yv * yv;
+        } else {
+          const TX t2 = __builtin_fmaf(yv, yv, -comp[h]);
+          const TX s2 = acc[h] + t2;
+          comp[h] = (s2 - acc[h]) - t2;
+          acc[h] = s2;
+        }
+      } else if constexpr (sizeof(TX) == 4) {
+        acc[h] = __builtin_fmaf(yv, yv, acc[h]);
+      } else {
+        acc[0] = __builtin_fma(yv, yv, acc[0]);
+      }
+    }
+  if constexpr (sizeof(TX) == 4 && KAHAN) return (acc[0] - comp[0]) + (acc[1] - comp[1]);
+  else if constexpr (sizeof(TX) == 4) return acc[0] + acc[1];
+  else return acc[0];
+}
+
+// Copies of the lane number and of a uniform value that the compiler takes for
+// new: what a side derives from them is then computed inside the side's code,
+// where it would otherwise be hoisted out of the loop over the sides, for every
+// side, into registers.
+__device__ __forceinline__ int fresh(int lane) {
+  __asm__ volatile("" : "+v"(lane));
+  return lane;
+}
+__device__ __forceinline__ int fresh_uniform(int v) {
+  v = __builtin_amdgcn_readfirstlane(v);
+  __asm__ volatile("" : "+s"(v));
+  return v;
+}
+
+// ---------------------------------------------------------------- control block
+// Order-preserving map of doubles to unsigned 64-bit keys (for atomic max).
+__device__ __forceinline__ unsigned long long dkey(double d) {
+  unsigned long long u = (unsigned long long)__double_as_longlong(d);
+  return (u >> 63) ? ~u : (u | 0x8000000000000000ull);
+}
+__host__ __device__ inline double dkey_inv(unsigned long long k) {
+  unsigned long long u = (k >> 63) ? (k & 0x7FFFFFFFFFFFFFFFull) : ~k;
+  double d;
+  __builtin_memcpy(&d, &u, 8);
+  return d;
+}
+
+// atomicMax of a key that skips the atomic when the stored key is already at
+// least as large (a stale read only costs an unneeded atomic): with many
+// blocks reporting into one address most of them then skip it.
+__device__ __forceinline__ void key_max(unsigned long long* addr, unsigned long long k) {
+  if (k > __hip_atomic_load(addr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(addr, k);
+}
+
+struct Ctrl {
+  int done;            // converged flag read by every sweep kernel
+  int done_sweep;      // sweep at which it converged
+  int nonfinite;       // input check result
+  int abort;           // a sweep kernel's producer/consumer wait gave up
+  unsigned long long delta_key;  // running max |x - prev| of the checked sweep
+  double last_delta;
+  unsigned long long viol_key;   // running max violation
+  unsigned long long icd_sum[4]; // an ICD call's summed work counters
+  unsigned int nf_epoch;         // last ICD call (by its number) whose input was not finite
+  int ticket[2];       // next job of a sweep launch: odd and even sweeps
+  int arrived;         // check jobs of the sweep that have ended
+  int streamed;        // regions of the sweep streamed whole
+};
+
 // ---------------------------------------------------------------- LDS counters
 __device__ __forceinline__ int lds_load(const int* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -318,12 +411,13 @@ struct ImageDesc {
   const RoundEntry* rtab;  // round tables, [side][class][round_table_len(R)]
   int64_t ld;
   int64_t q_byte;       // first byte of this image's increments in the stream
+  int64_t live_off;     // its live bits, bytes from there (layout in sparse.hpp)
   int32_t H, W;
   int32_t nrx, nry;     // region grid
   int32_t fr;           // footprint side R + smax - 1
   int32_t nsides;
   float guard;          // FP32 recheck band (relative)
-  int32_t pad;
+  int32_t stream;       // every region through region_job
   int32_t sides[kMaxSides];  // descending
   float r2f[kMaxSides];
   float rf[kMaxSides];       // sqrt(r2), FP32
@@ -355,10 +449,12 @@ struct WorkItem {
 // Bounded wait until *ctr >= target; returns the last value read (SGPR).
 // When the bound is hit, or the other wave has given up, the abort flag is set
 // and the wait returns, so every wave of the workgroup finishes.
-__device__ __forceinline__ int wait_ge(const int* ctr, int target, int* abort) {
+__device__ __forceinline__ int wait_ge(const int* ctr, int target, int* abort,
+                                       int limit = kSpinLimit) {
   int seen = __builtin_amdgcn_readfirstlane(lds_load(ctr));
+#pragma nounroll
   for (int spin = 0; seen < target; ++spin) {
-    if (spin >= kSpinLimit || lds_load(abort)) {
+    if (spin >= limit || lds_load(abort)) {
       lds_store(abort, 1);
       return target;
     }
@@ -366,6 +462,17 @@ __device__ __forceinline__ int wait_ge(const int* ctr, int target, int* abort) {
     seen = __builtin_amdgcn_readfirstlane(lds_load(ctr));
   }
   return seen;
+}
+
+// Image pixels.  `shared`: they go from one workgroup to others of the same launch,
+// on any XCD, so loads and stores are coherent across the device (slower: they
+// pass by the XCD's L2).
+template <typename TX> __device__ __forceinline__ TX load_pixel(const TX* p, bool shared) {
+  return shared ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *p;
+}
+template <typename TX> __device__ __forceinline__ void store_pixel(TX* p, TX v, bool shared) {
+  if (shared) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else *p = v;
 }
 
 struct Consumer {
@@ -391,14 +498,14 @@ __device__ __forceinline__ void run_side(const ImageDesc& a, Consumer& c, TX* xs
   constexpr uint32_t RMASK = kSlots * kPage - 1;
   using QS = QStore<TQ, TX>;
 
-  const int wl = c.lane / G, jj = c.lane % G;
+  const int lane = c.lane, wl = lane / G, jj = lane % G;
   const int bry = wl / BC, brx = wl % BC, jr = jj / GC, jc = jj % GC;
   const bool rl = jr < JRL, cl = jc < JCL;     // lane holds a pixel in the last row / col slot
   const int ef = jr * GC + jc, el = jr * JCL + jc;  // element of the lane inside a slot
   const int lane_x0 = (S * bry + jr) * P + (S * brx + jc);
   // per-lane dummy targets for the writes of masked lanes
-  const int xdum = LS::XDUMMY + c.lane;
-  const uint32_t qdum = (uint32_t)(LS::QD + c.lane * ES);
+  const int xdum = LS::XDUMMY + lane;
+  const uint32_t qdum = (uint32_t)(LS::QD + lane * ES);
   if (nrounds <= 0) return;
   // per-side constants live in VGPRs (the loop would otherwise reload them)
   TX r2 = (sizeof(TX) == 8) ? (TX)a.r2d[k] : (TX)a.r2f[k];
@@ -459,50 +566,17 @@ __device__ __forceinline__ void run_side(const ImageDesc& a, Consumer& c, TX* xs
       }
     // 2) y = x + I (pixels outside the window count as 0), sum of squares
     TX y[U][V];
-    // FP32: two interleaved accumulators (even / odd elements), each with its
-    // own compensation when KAHAN, so the dependent add chains are half as
-    // long; the corrected partial sums are added at the end.
-    TX acc[2] = {0, 0}, comp[2] = {0, 0};
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int v = 0; v < V; ++v) {
-        TX yv = xv[u][v] + qv[u][v];
-        const bool part_r = (u == U - 1) && (JRL < GR);
-        const bool part_c = (v == V - 1) && (JCL < GC);
-        if (part_r && part_c) yv = (rl && cl) ? yv : TX(0);
-        else if (part_r) yv = rl ? yv : TX(0);
-        else if (part_c) yv = cl ? yv : TX(0);
-        y[u][v] = yv;
-        const int h = (sizeof(TX) == 4) ? ((u * V + v) & 1) : 0;
-        if constexpr (sizeof(TX) == 4 && KAHAN) {
-          if (u * V + v < 2) {
-            // an accumulator's first term: the compensated step from (0, 0)
-            // gives acc = y^2 rounded and comp = 0 exactly (finite y), so
-            // take those values instead of computing y^2 - y^2
-            acc[h] = yv * yv;
-          } else {
-            const TX t2 = __builtin_fmaf(yv, yv, -comp[h]);
-            const TX s2 = acc[h] + t2;
-            comp[h] = (s2 - acc[h]) - t2;
-            acc[h] = s2;
-          }
-        } else if constexpr (sizeof(TX) == 4) {
-          acc[h] = __builtin_fmaf(yv, yv, acc[h]);
-        } else {
-          acc[0] = __builtin_fma(yv, yv, acc[0]);
-        }
-      }
-    TX lane_sum;
-    if constexpr (sizeof(TX) == 4 && KAHAN) lane_sum = (acc[0] - comp[0]) + (acc[1] - comp[1]);
-    else if constexpr (sizeof(TX) == 4) lane_sum = acc[0] + acc[1];
-    else lane_sum = acc[0];
+      for (int v = 0; v < V; ++v) y[u][v] = xv[u][v] + qv[u][v];
+    const TX lsum = lane_sum<TX, R, S, KAHAN>(y, rl, cl);
     // the next round's byte end into a scalar register here, mid-round, so
     // the vector-to-scalar hand-off is long done when the loop test and the
     // next round's page check use it
     uint32_t rb_end_n = __builtin_amdgcn_readfirstlane(en.y);
     __asm__ volatile("" : "+s"(rb_end_n));
-    const TX n = group_sum<G>(lane_sum);
+    const TX n = group_sum<G>(lsum);
 
     // 3) x' = t y into the footprint, I' = y - x' into the ring (pixels
     //    first, then increments, so neighbouring writes merge)
@@ -564,7 +638,7 @@ __device__ __forceinline__ void run_side(const ImageDesc& a, Consumer& c, TX* xs
     if (__builtin_expect(roff + nbytes > (uint32_t)(kSlots * kPage), 0)) {
       const int np = (int)((roff + nbytes - kSlots * kPage + kPage - 1) / kPage);
       u32x4* r4 = (u32x4*)c.ring;
-      for (int p = 0; p < np; ++p) r4[p * 64 + c.lane] = r4[(kSlots + p) * 64 + c.lane];
+      for (int p = 0; p < np; ++p) r4[p * 64 + lane] = r4[(kSlots + p) * 64 + lane];
     }
     __asm__ volatile("" ::: "memory");
     lds_store(c.consumed, (int)((qb0 + rb_end) / kPage));
@@ -651,18 +725,19 @@ template <typename TX, typename TQ, int R, int SMAX> struct PhaseLds {
   int ctr[3];  // pages ready, pages consumed, abort flag
 };
 
-// One region of one image: both waves of the workgroup enter; the caller
-// resets the counters and synchronises the workgroup before and after.
-template <typename TX, typename TQ, int R, int SMAX, bool KAHAN>
+// One region of one image: two waves of the workgroup enter; the caller
+// resets the counters and synchronises the workgroup before and after.  ready():
+// waits until the region's pixels may be read (the increments may be at once);
+// ended(): called once they are stored.
+template <typename TX, typename TQ, int R, int SMAX, bool KAHAN, typename Ready, typename Ended>
 __device__ __forceinline__ void region_job(const ImageDesc& a, int region, unsigned char* q,
-                                           PhaseLds<TX, TQ, R, SMAX>& L) {
+                                           PhaseLds<TX, TQ, R, SMAX>& L, int lane, bool shared,
+                                           const Ready& ready, const Ended& ended) {
   using SH = PhaseShape<TX, TQ, R, SMAX>;
   const int ry = region / a.nrx, rx = region - (region / a.nrx) * a.nrx;
   const RegionStream st = a.rs[region];
   const int npg = st.npages;
-  const int lane = threadIdx.x & 63;
-
-  if (threadIdx.x >= 64) {
+  if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) != 0) {
     produce<SH::MIRROR>((u32x4*)(q + a.q_byte) + (int64_t)st.first * 64, npg, st.stride,
                         (u32x4*)L.ring, &L.ctr[0], &L.ctr[1], &L.ctr[2], lane);
     return;
@@ -672,9 +747,10 @@ __device__ __forceinline__ void region_job(const ImageDesc& a, int region, unsig
   const int fh = min(a.fr, a.H - r0), fw = min(a.fr, a.W - c0);
   TX* xg = (TX*)a.x;
   TX* xs = L.xs;
+  ready();
   for (int idx = lane; idx < fh * fw; idx += 64) {
     const int i = idx / fw, j = idx - (idx / fw) * fw;
-    xs[i * SH::P + j] = xg[(int64_t)(r0 + i) * a.ld + c0 + j];
+    xs[i * SH::P + j] = load_pixel(xg + (int64_t)(r0 + i) * a.ld + c0 + j, shared);
   }
   __asm__ volatile("" ::: "memory");
 
@@ -722,7 +798,11 @@ __device__ __forceinline__ void region_job(const ImageDesc& a, int region, unsig
 
   for (int idx = lane; idx < fh * fw; idx += 64) {
     const int i = idx / fw, j = idx - (idx / fw) * fw;
-    xg[(int64_t)(r0 + i) * a.ld + c0 + j] = xs[i * SH::P + j];
+    store_pixel(xg + (int64_t)(r0 + i) * a.ld + c0 + j, xs[i * SH::P + j], shared);
+  }
+  if (shared) {
+    __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    ended();
   }
 }
 
@@ -734,49 +814,6 @@ __device__ __forceinline__ void reset_counters(PhaseLds<TX, TQ, R, SMAX>& L) {
     L.ctr[2] = 0;
   }
   __syncthreads();
-}
-
-// A wait inside the region job gave up (a protocol failure): raise the
-// caller's flag -- the single-image call's control block or the image's
-// batch control block -- which the host reports as a device error for that
-// solve only.
-template <typename TX, typename TQ, int R, int SMAX>
-__device__ __forceinline__ void report_abort(PhaseLds<TX, TQ, R, SMAX>& L, int* flag) {
-  __syncthreads();
-  if (threadIdx.x == 0 && L.ctr[2]) atomicOr(flag, 1);
-}
-
-// One image, one colour: block b takes the b-th region of colour (cy, cx).
-template <typename TX, typename TQ, int R, int SMAX, bool KAHAN>
-__global__ __launch_bounds__(128) void region_phase(ImageDesc a, int cy, int cx, int ncx,
-                                                    const int* done, int* abort_flag,
-                                                    unsigned char* q) {
-  __shared__ PhaseLds<TX, TQ, R, SMAX> L;
-  if (*done) return;
-  const int b = blockIdx.x;
-  const int region = (cy + 2 * (b / ncx)) * a.nrx + cx + 2 * (b % ncx);
-  reset_counters(L);
-  region_job<TX, TQ, R, SMAX, KAHAN>(a, region, q, L);
-  report_abort(L, abort_flag);
-}
-
-// A batch of images, one colour: a persistent grid walks the colour's work
-// list; items of converged images are skipped.
-template <typename TX, typename TQ, int R, int SMAX, bool KAHAN>
-__global__ __launch_bounds__(128) void region_phase_batch(const ImageDesc* __restrict__ imgs,
-                                                          BatchCtl* __restrict__ ctl,
-                                                          const WorkItem* __restrict__ items,
-                                                          const int* __restrict__ nitems,
-                                                          unsigned char* q) {
-  __shared__ PhaseLds<TX, TQ, R, SMAX> L;
-  const int n = *nitems;
-  for (int it = blockIdx.x; it < n; it += gridDim.x) {
-    const WorkItem w = items[it];
-    if (ctl[w.img].done) continue;
-    reset_counters(L);
-    region_job<TX, TQ, R, SMAX, KAHAN>(imgs[w.img], w.region, q, L);
-    report_abort(L, &ctl[w.img].aborted);
-  }
 }
 
 }  // namespace smre

@@ -26,6 +26,7 @@
 #include "icd.hpp"
 #include "checks.hpp"
 #include "kernels.hpp"
+#include "sparse.hpp"
 #include "mc.hpp"
 #include "canon.hpp"
 #include "icd_nested.hpp"
@@ -78,7 +79,8 @@ struct smre_ctx {
 
 namespace {
 
-constexpr int kLag = 4;  // host reads the converged flag this many checks late
+constexpr int kLag = 4;    // host reads the converged flag this many checks late
+constexpr int kAhead = 2;  // (single image) sweeps between two looks at it
 
 int set_device(smre_ctx* c) {
   HIP_OK(hipSetDevice(c->device));
@@ -140,11 +142,12 @@ struct Plan {
   int nry = 0, nrx = 0;
   int64_t nq = 0;  // increment elements
   int64_t nwin = 0;
-  size_t qbytes = 0;
-  size_t off_roff = 0, off_prev = 0, off_isum = 0, off_sig = 0, total = 0;
+  size_t live_off = 0, qbytes = 0;  // increments, then live bits
+  size_t off_roff = 0, off_prog = 0, off_prev = 0, off_isum = 0, off_sig = 0, total = 0;
   std::vector<RegionStream> roff;  // page layout of each region's increments
-  // device metadata blob: the region streams, then (16-byte aligned) the round
-  // tables; meta_bytes covers both whether or not the blob is built
+  // device metadata blob: the region streams, the image's descriptor (filled in
+  // by a single-image call), then (aligned) the round tables; meta_bytes covers
+  // them whether or not the blob is built
   std::vector<unsigned char> meta;
   size_t meta_rtab = 0, meta_bytes = 0;
 };
@@ -307,8 +310,11 @@ int plan_project(smre_dtype dt, int64_t H, int64_t W, const smre_params* p, Plan
   }
   pl->nq = nq;
   pl->nwin = nwin;
-  pl->qbytes = (size_t)(pages + 1) * kPage;
-  pl->meta_rtab = align_up((size_t)nreg * sizeof(RegionStream), 256);
+  // the live bits of every region follow the increments (both start at zero)
+  pl->live_off = (size_t)(pages + 1) * kPage;
+  pl->qbytes = pl->live_off +
+               align_up((size_t)nreg * (kLiveHead + pl->nsides * live_words(pl->R)) * 4, 256);
+  pl->meta_rtab = align_up((size_t)nreg * sizeof(RegionStream) + sizeof(ImageDesc), 256);
   pl->meta_bytes =
       pl->meta_rtab + (size_t)pl->nsides * 9 * round_table_len(pl->R) * sizeof(RoundEntry);
   if (need_offsets) {
@@ -317,7 +323,8 @@ int plan_project(smre_dtype dt, int64_t H, int64_t W, const smre_params* p, Plan
     build_round_tables(*pl, H, W, es, (RoundEntry*)(pl->meta.data() + pl->meta_rtab));
   }
   pl->off_roff = pl->qbytes;
-  pl->off_prev = align_up(pl->off_roff + pl->meta_bytes, 256);
+  pl->off_prog = align_up(pl->off_roff + pl->meta_bytes, 256);
+  pl->off_prev = align_up(pl->off_prog + (size_t)nreg * 4, 256);
   pl->off_isum = align_up(pl->off_prev + (size_t)H * W * xs, 256);
   pl->off_sig = align_up(pl->off_isum + (size_t)H * W * xs, 256);
   pl->total = align_up(pl->off_sig + kSigWords * sizeof(uint64_t), 256);
@@ -369,43 +376,64 @@ int ensure_ctrl(smre_ctx* c) {
 int grid_for(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>(8192, (n + 255) / 256)); }
 int grid_rows(int64_t H) { return (int)std::max<int64_t>(1, std::min<int64_t>(4096, H)); }
 
-// One colour of one image: grid = regions of that colour.
-struct PhaseLaunch {
-  int cy, cx, ncx, blocks;
-  const int* done;
-  int* abort;  // raised by a region job whose producer/consumer wait gave up
-  unsigned char* q;
+// One launch of the sweep kernel, or (st given) of stream_phase for a colour, or
+// (sb) of stream_batch.
+struct StreamLaunch {
+  ImageDesc a;
+  int cy, cx, ncx;
 };
 
 template <typename TX, typename TQ, int R, int SMAX, bool KAHAN>
-void launch_phase(const ImageDesc& a, const PhaseLaunch& l, hipStream_t s) {
-  hipLaunchKernelGGL((region_phase<TX, TQ, R, SMAX, KAHAN>), dim3(l.blocks), dim3(128), 0, s, a,
-                     l.cy, l.cx, l.ncx, l.done, l.abort, l.q);
+void launch_either(int grid, const PhaseArgs& p, const StreamLaunch* st, bool stream_batch,
+                   hipStream_t s) {
+  if (st) launch_stream<TX, TQ, R, SMAX, KAHAN>(st->a, st->cy, st->cx, st->ncx, grid, p, s);
+  else launch_phase<TX, TQ, R, SMAX, KAHAN>(grid, p, stream_batch, s);
 }
 
 template <typename TX, typename TQ, bool KAHAN>
-int launch_phase_r(int R, int SI, const ImageDesc& a, const PhaseLaunch& l, hipStream_t s) {
+int launch_phase_r(int R, int SI, int grid, const PhaseArgs& p, const StreamLaunch* st, bool sb,
+                   hipStream_t s) {
   switch (R) {
-    case 8: launch_phase<TX, TQ, 8, 9, KAHAN>(a, l, s); break;
+    case 8: launch_either<TX, TQ, 8, 9, KAHAN>(grid, p, st, sb, s); break;
     case 16:
-      if (SI == 9) launch_phase<TX, TQ, 16, 9, KAHAN>(a, l, s);
-      else launch_phase<TX, TQ, 16, 17, KAHAN>(a, l, s);
+      if (SI == 9) launch_either<TX, TQ, 16, 9, KAHAN>(grid, p, st, sb, s);
+      else launch_either<TX, TQ, 16, 17, KAHAN>(grid, p, st, sb, s);
       break;
-    case 32: launch_phase<TX, TQ, 32, 33, KAHAN>(a, l, s); break;
+    case 32: launch_either<TX, TQ, 32, 33, KAHAN>(grid, p, st, sb, s); break;
     default: return SMRE_EINVAL;
   }
   HIP_OK(hipGetLastError());
   return SMRE_OK;
 }
 
-int launch_phase_any(smre_dtype dt, int inc, int kahan, int R, int SI, const ImageDesc& a,
-                     const PhaseLaunch& l, hipStream_t s) {
-  if (dt == SMRE_F64) return launch_phase_r<double, double, false>(R, SI, a, l, s);
+int launch_phase_any(smre_dtype dt, int inc, int kahan, int R, int SI, int grid,
+                     const PhaseArgs& p, hipStream_t s, const StreamLaunch* st = nullptr,
+                     bool sb = false) {
+  if (dt == SMRE_F64) return launch_phase_r<double, double, false>(R, SI, grid, p, st, sb, s);
   if (inc == SMRE_INC_BF16)
-    return kahan ? launch_phase_r<float, bf16_t, true>(R, SI, a, l, s)
-                 : launch_phase_r<float, bf16_t, false>(R, SI, a, l, s);
-  return kahan ? launch_phase_r<float, float, true>(R, SI, a, l, s)
-               : launch_phase_r<float, float, false>(R, SI, a, l, s);
+    return kahan ? launch_phase_r<float, bf16_t, true>(R, SI, grid, p, st, sb, s)
+                 : launch_phase_r<float, bf16_t, false>(R, SI, grid, p, st, sb, s);
+  return kahan ? launch_phase_r<float, float, true>(R, SI, grid, p, st, sb, s)
+               : launch_phase_r<float, float, false>(R, SI, grid, p, st, sb, s);
+}
+
+template <typename TX> void launch_check(int R, const PhaseArgs& p, hipStream_t s) {
+  const dim3 grid(p.ncheck), block(256);
+  if (R == 8) hipLaunchKernelGGL((sweep_check_kernel<TX, 8>), grid, block, 0, s, p);
+  else if (R == 16) hipLaunchKernelGGL((sweep_check_kernel<TX, 16>), grid, block, 0, s, p);
+  else hipLaunchKernelGGL((sweep_check_kernel<TX, 32>), grid, block, 0, s, p);
+}
+
+// Few rounds in a region: streaming its increments whole costs less than finding
+// out what may be left out (24 rounds in FP64: 10 against 14 us a colour).
+constexpr int kStreamRounds = 100;
+int streams_all(const Plan& pl) {
+  int rounds = 0;
+  for (int k = 0; k < pl.nsides; ++k) {
+    const int n = axis_rounds(pl.R, pl.sides[k]);
+    rounds += n * n;
+  }
+  return rounds <= kStreamRounds;
 }
 
 // Feasibility of frames stacked fstride elements apart over the sides (each
@@ -509,7 +537,7 @@ int check_nonfinite(smre_ctx* c, const void* x, int64_t H, int64_t W, int64_t ld
 
 template <typename TX>
 int project_impl(smre_ctx* c, smre_dtype dt, void* x, int64_t H, int64_t W, int64_t ld,
-                 const smre_params* p, const Plan& pl, unsigned char* ws, hipStream_t s,
+                 const smre_params* p, Plan& pl, unsigned char* ws, hipStream_t s,
                  smre_report* rep) {
   const size_t es = (p->inc == SMRE_INC_BF16) ? 2 : sizeof(TX);
   HIP_OK(hipEventRecord(c->t0, s));
@@ -523,12 +551,12 @@ int project_impl(smre_ctx* c, smre_dtype dt, void* x, int64_t H, int64_t W, int6
   problem_signature(dt, H, W, p, pl, sig);
   TX* isum = (TX*)(ws + pl.off_isum);
   uint64_t* dsig = (uint64_t*)(ws + pl.off_sig);
+  uint64_t have[kSigWords] = {};
   if (p->warm) {
     // the increments (and sum_S I_S) of the previous solve of this problem
-    uint64_t have[kSigWords];
     HIP_OK(hipMemcpyAsync(have, dsig, sizeof have, hipMemcpyDeviceToHost, s));
     HIP_OK(hipStreamSynchronize(s));
-    if (std::memcmp(have, sig, sizeof sig) != 0) return SMRE_EINVAL;
+    if (std::memcmp(have, sig, sizeof sig - sizeof sig[7]) != 0) return SMRE_EINVAL;
     hipLaunchKernelGGL((warm_begin_kernel<TX>), dim3(grid_rows(H)), dim3(256), 0, s, (TX*)x, ld,
                        (int)H, (int)W, isum);
   } else {
@@ -543,15 +571,13 @@ int project_impl(smre_ctx* c, smre_dtype dt, void* x, int64_t H, int64_t W, int6
   hipLaunchKernelGGL((fill_kernel<uint64_t>), dim3(1), dim3(256), 0, s, dsig, (int64_t)kSigWords,
                      (uint64_t)0);
   HIP_OK(hipGetLastError());
-  HIP_OK(hipMemcpyAsync(ws + pl.off_roff, pl.meta.data(), pl.meta.size(), hipMemcpyHostToDevice,
-                        s));
-
   ImageDesc a{};
   a.x = x;
   a.rs = (const RegionStream*)(ws + pl.off_roff);
   a.rtab = (const RoundEntry*)(ws + pl.off_roff + pl.meta_rtab);
   a.ld = ld;
   a.q_byte = 0;
+  a.live_off = (int64_t)pl.live_off;
   a.H = (int)H;
   a.W = (int)W;
   a.nrx = pl.nrx;
@@ -565,53 +591,70 @@ int project_impl(smre_ctx* c, smre_dtype dt, void* x, int64_t H, int64_t W, int6
     a.rf[k] = (float)std::sqrt(pl.r2[k]);
     a.r2d[k] = pl.r2[k];
   }
+  const size_t desc_at = (size_t)pl.nrx * pl.nry * sizeof(RegionStream);
+  std::memcpy(pl.meta.data() + desc_at, &a, sizeof a);
+  HIP_OK(hipMemcpyAsync(ws + pl.off_roff, pl.meta.data(), pl.meta.size(), hipMemcpyHostToDevice,
+                        s));
   TX* prev = (TX*)(ws + pl.off_prev);
   const bool checking = p->tol > 0;
+  auto checked = [&](int k) {
+    return checking && (k % p->check_every == 0 || k == p->max_sweeps);
+  };
+  int* progress = (int*)(ws + pl.off_prog);
+  const int64_t nreg = (int64_t)pl.nry * pl.nrx;
+  hipLaunchKernelGGL((fill_kernel<int>), dim3(grid_for(nreg)), dim3(256), 0, s, progress, nreg, 0);
+  if (checked(1))
+    hipLaunchKernelGGL((snapshot_kernel<TX>), dim3(grid_rows(H)), dim3(256), 0, s, (const TX*)x,
+                       ld, (int)H, (int)W, prev, c->ctrl);
+  PhaseArgs l{};
+  l.imgs = (const ImageDesc*)(ws + pl.off_roff + desc_at);
+  l.done = &c->ctrl->done;
+  l.abort = &c->ctrl->abort;
+  l.q = ws;
+  for (int k = 0; k < 4; ++k)
+    l.nregions[k] = ((pl.nry - (k >> 1) + 1) / 2) * ((pl.nrx - (k & 1) + 1) / 2);
+  l.tol = p->tol;
+  l.progress = progress;
+  l.prev = prev;
+  l.ctrl = c->ctrl;
+  l.host_done = c->counters_host;
+  c->counters_host[0] = c->counters_host[1] = 0;
+  // sig[7]: the increments kept for a warm start have no live bits
+  bool stream = streams_all(pl) || (p->warm && have[7] != 0);
+  // as many workgroups as a colour has regions, at most what the device holds
+  // (further ones would only find the tickets taken)
+  const int grid = std::max(1, std::min(l.nregions[0], 4 * c->cus));
   TimingAcc tacc;
-  std::deque<std::pair<int, int>> inflight;  // (lag slot, sweep)
-  int lag_slot = 0;
-  bool host_done = false;
   int sweep = 0;
-  for (sweep = 1; sweep <= p->max_sweeps && !host_done; ++sweep) {
-    const bool check = checking && (sweep % p->check_every == 0 || sweep == p->max_sweeps);
-    if (check)
-      hipLaunchKernelGGL((snapshot_kernel<TX>), dim3(grid_rows(H)), dim3(256), 0, s,
-                         (const TX*)x, ld, (int)H, (int)W, prev, c->ctrl);
-    for (int color = 0; color < 4; ++color) {
-      PhaseLaunch l;
-      l.cy = color >> 1;
-      l.cx = color & 1;
-      const int ny = (pl.nry - l.cy + 1) / 2, nx = (pl.nrx - l.cx + 1) / 2;
-      l.ncx = nx;
-      l.blocks = ny * nx;
-      l.done = &c->ctrl->done;
-      l.abort = &c->ctrl->abort;
-      l.q = ws;
-      if (ny <= 0 || nx <= 0) continue;
+  for (sweep = 1; sweep <= p->max_sweeps; ++sweep) {
+    l.sweep = sweep;
+    l.decide = checked(sweep);
+    // (the sweep before a checked one keeps the image)
+    l.ncheck = l.decide || (sweep < p->max_sweeps && checked(sweep + 1)) ? l.nregions[0] : 0;
+    for (int color = 0; color < (stream ? 4 : 1); ++color) {
+      StreamLaunch st{a, color >> 1, color & 1, (pl.nrx - (color & 1) + 1) / 2};
+      const int jobs = stream ? l.nregions[color] : grid;
+      if (jobs == 0) continue;
       int slot;
       rc = timing_begin(c, tacc, s, &slot);
       if (rc) return rc;
-      rc = launch_phase_any(dt, p->inc, p->kahan, pl.R, pl.SI, a, l, s);
+      rc = launch_phase_any(dt, p->inc, p->kahan, pl.R, pl.SI, jobs, l, s, stream ? &st : nullptr);
       if (rc) return rc;
       rc = timing_end(c, tacc, s, slot);
       if (rc) return rc;
     }
-    if (check) {
-      hipLaunchKernelGGL((delta_kernel<TX>), dim3(grid_rows(H)), dim3(256), 0, s,
-                         (const TX*)x, ld, (int)H, (int)W, (const TX*)prev, c->ctrl);
-      hipLaunchKernelGGL(decide_kernel, dim3(1), dim3(1), 0, s, c->ctrl, p->tol, sweep);
-      HIP_OK(hipGetLastError());
-      HIP_OK(hipMemcpyAsync(c->ctrl_host + 1 + lag_slot, c->ctrl, sizeof(Ctrl),
-                            hipMemcpyDeviceToHost, s));
-      HIP_OK(hipEventRecord(c->lag_ev[lag_slot], s));
-      inflight.push_back({lag_slot, sweep});
-      lag_slot = (lag_slot + 1) % (kLag + 1);
-      if ((int)inflight.size() > kLag) {
-        auto f = inflight.front();
-        inflight.pop_front();
-        HIP_OK(hipEventSynchronize(c->lag_ev[f.first]));
-        if (c->ctrl_host[1 + f.first].done) host_done = true;
-      }
+    if (stream && l.ncheck) launch_check<TX>(pl.R, l, s);
+    // the host stays at most 2 kAhead sweeps ahead; sweeps queued past the last
+    // one find the flag and end at once
+    if (checking && sweep % kAhead == 0) {
+      const int e = sweep / kAhead % 2;
+      if (sweep > kAhead) HIP_OK(hipEventSynchronize(c->lag_ev[1 - e]));
+      const volatile int* seen = c->counters_host;
+      if (seen[0]) break;
+      // most regions stream: the leaner kernel is faster at that, and what it
+      // leaves out (the live bits) is not needed again in this problem
+      if (!stream && 3 * seen[1] > nreg) stream = true;
+      HIP_OK(hipEventRecord(c->lag_ev[e], s));
     }
   }
   // sum_S I_S = x0 - z for a later warm start
@@ -624,6 +667,7 @@ int project_impl(smre_ctx* c, smre_dtype dt, void* x, int64_t H, int64_t W, int6
   HIP_OK(hipMemcpy(c->ctrl_host, c->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost));
   const Ctrl fin = *c->ctrl_host;
   const int sweeps_run = fin.done ? fin.done_sweep : p->max_sweeps;
+  sig[7] = stream;
   if (!fin.abort)  // the increments belong to this problem now
     HIP_OK(hipMemcpy(dsig, sig, sizeof sig, hipMemcpyHostToDevice));
   double viol = 0.0;
@@ -1237,6 +1281,7 @@ struct BatchPlan {
   int R = 16;
   int SI = 17;  // kernel instance shared by every image (instance_smax of the batch)
   int n = 0;
+  bool stream = true;  // every image's regions are streamed whole (streams_all)
   std::vector<Plan> plans;
   std::vector<size_t> qoff;       // byte offset of each image's increments
   std::vector<size_t> roff_off;   // byte offset of each image's metadata blob
@@ -1256,6 +1301,7 @@ int plan_batch(smre_dtype dt, int n, const smre_batch_image* im, const smre_batc
     for (int k = 0; k < im[i].n_sides && im[i].sides; ++k)
       smax_all = std::max(smax_all, (int)im[i].sides[k]);
   B->SI = instance_smax(R, smax_all);
+  B->stream = true;
   B->plans.assign(n, Plan());
   B->qoff.assign(n, 0);
   B->roff_off.assign(n, 0);
@@ -1279,6 +1325,7 @@ int plan_batch(smre_dtype dt, int n, const smre_batch_image* im, const smre_batc
     if (!im[i].x || im[i].ld < im[i].W) return SMRE_EINVAL;
     int rc = plan_project(dt, im[i].H, im[i].W, &p, &B->plans[i], need_offsets, B->SI);
     if (rc) return rc;
+    B->stream = B->stream && streams_all(B->plans[i]);
     B->qoff[i] = B->qbytes;
     B->qbytes += align_up(B->plans[i].qbytes, kPage);
     B->roff_off[i] = B->roff_elems;
@@ -1301,47 +1348,20 @@ int plan_batch(smre_dtype dt, int n, const smre_batch_image* im, const smre_batc
 }
 
 template <typename TX, typename TQ, int R, int SMAX, bool KAHAN>
-int batch_grid(int cus, int want) {
+int batch_grid(int cus, int want, bool stream) {
   int occ = 0;
-  HIP_OK(hipOccupancyMaxActiveBlocksPerMultiprocessor(
-      &occ, (const void*)region_phase_batch<TX, TQ, R, SMAX, KAHAN>, 128, 0));
+  HIP_OK((phase_blocks<TX, TQ, R, SMAX, KAHAN>(&occ, stream)));
   return std::max(1, std::min(want, std::max(1, occ) * cus));
 }
 
 template <typename TX, typename TQ, bool KAHAN>
-int launch_batch_phase(int R, int SI, int grid, const ImageDesc* d, BatchCtl* ctl,
-                       const WorkItem* items, const int* cnt, unsigned char* q, hipStream_t s) {
+int grid_for_batch(smre_ctx* c, int R, int SI, int want, bool stream) {
   switch (R) {
-    case 8:
-      hipLaunchKernelGGL((region_phase_batch<TX, TQ, 8, 9, KAHAN>), dim3(grid), dim3(128), 0, s, d,
-                         ctl, items, cnt, q);
-      break;
+    case 8: return batch_grid<TX, TQ, 8, 9, KAHAN>(c->cus, want, stream);
     case 16:
-      if (SI == 9)
-        hipLaunchKernelGGL((region_phase_batch<TX, TQ, 16, 9, KAHAN>), dim3(grid), dim3(128), 0,
-                           s, d, ctl, items, cnt, q);
-      else
-        hipLaunchKernelGGL((region_phase_batch<TX, TQ, 16, 17, KAHAN>), dim3(grid), dim3(128), 0,
-                           s, d, ctl, items, cnt, q);
-      break;
-    case 32:
-      hipLaunchKernelGGL((region_phase_batch<TX, TQ, 32, 33, KAHAN>), dim3(grid), dim3(128), 0, s,
-                         d, ctl, items, cnt, q);
-      break;
-    default: return SMRE_EINVAL;
-  }
-  HIP_OK(hipGetLastError());
-  return SMRE_OK;
-}
-
-template <typename TX, typename TQ, bool KAHAN>
-int grid_for_batch(smre_ctx* c, int R, int SI, int want) {
-  switch (R) {
-    case 8: return batch_grid<TX, TQ, 8, 9, KAHAN>(c->cus, want);
-    case 16:
-      return SI == 9 ? batch_grid<TX, TQ, 16, 9, KAHAN>(c->cus, want)
-                     : batch_grid<TX, TQ, 16, 17, KAHAN>(c->cus, want);
-    default: return batch_grid<TX, TQ, 32, 33, KAHAN>(c->cus, want);
+      return SI == 9 ? batch_grid<TX, TQ, 16, 9, KAHAN>(c->cus, want, stream)
+                     : batch_grid<TX, TQ, 16, 17, KAHAN>(c->cus, want, stream);
+    default: return batch_grid<TX, TQ, 32, 33, KAHAN>(c->cus, want, stream);
   }
 }
 
@@ -1356,30 +1376,26 @@ struct BatchDev {
   int grid[4];
   int n;
   int maxh;
+  bool stream = false;  // stream_batch
 };
 
 template <typename TX>
 int enqueue_batch_sweep(smre_dtype dt, const smre_batch_params* bp, int R, int SI,
                         const BatchDev& D, bool check, hipStream_t s) {
-  (void)dt;
   const dim3 cg(std::max(1, std::min(64, D.maxh)), D.n);
   if (check)
     hipLaunchKernelGGL((snapshot_batch<TX>), cg, dim3(256), 0, s, D.desc, D.ctl, (TX*)D.prev);
   for (int color = 0; color < 4; ++color) {
-    int rc;
-    if (sizeof(TX) == 8)
-      rc = launch_batch_phase<double, double, false>(R, SI, D.grid[color], D.desc, D.ctl,
-                                                     D.items[color], D.cnt + color, D.q, s);
-    else if (bp->inc == SMRE_INC_BF16)
-      rc = bp->kahan ? launch_batch_phase<float, bf16_t, true>(R, SI, D.grid[color], D.desc, D.ctl,
-                                                                D.items[color], D.cnt + color, D.q, s)
-                     : launch_batch_phase<float, bf16_t, false>(R, SI, D.grid[color], D.desc, D.ctl,
-                                                                 D.items[color], D.cnt + color, D.q, s);
-    else
-      rc = bp->kahan ? launch_batch_phase<float, float, true>(R, SI, D.grid[color], D.desc, D.ctl,
-                                                               D.items[color], D.cnt + color, D.q, s)
-                     : launch_batch_phase<float, float, false>(R, SI, D.grid[color], D.desc, D.ctl,
-                                                                D.items[color], D.cnt + color, D.q, s);
+    PhaseArgs l{};
+    l.imgs = D.desc;
+    l.items = D.items[color];
+    l.nitems = D.cnt + color;
+    l.done = &D.ctl->done;
+    l.abort = &D.ctl->aborted;
+    l.flag_stride = sizeof(BatchCtl);
+    l.q = D.q;
+    const int rc =
+        launch_phase_any(dt, bp->inc, bp->kahan, R, SI, D.grid[color], l, s, nullptr, D.stream);
     if (rc) return rc;
   }
   if (check)
@@ -1411,6 +1427,7 @@ int batch_setup(smre_ctx* c, smre_dtype dt, int n, const smre_batch_image* im,
                      B.nitems[0] + B.nitems[1] + B.nitems[2]};
   int64_t fill[4] = {0, 0, 0, 0};
   D->maxh = 1;
+  D->stream = B.stream;
   for (int i = 0; i < n; ++i) {
     const Plan& pl = B.plans[i];
     std::memcpy(meta + B.roff_off[i], pl.meta.data(), pl.meta.size());
@@ -1420,6 +1437,7 @@ int batch_setup(smre_ctx* c, smre_dtype dt, int n, const smre_batch_image* im,
     a.rtab = (const RoundEntry*)(ws + B.off_roff + B.roff_off[i] + pl.meta_rtab);
     a.ld = im[i].ld;
     a.q_byte = (int64_t)B.qoff[i];
+    a.live_off = (int64_t)pl.live_off;
     a.H = (int)im[i].H;
     a.W = (int)im[i].W;
     a.nrx = pl.nrx;
@@ -1427,6 +1445,7 @@ int batch_setup(smre_ctx* c, smre_dtype dt, int n, const smre_batch_image* im,
     a.fr = pl.R + pl.smax - 1;
     a.nsides = pl.nsides;
     a.guard = (float)bp->guard_rel;
+    a.stream = streams_all(pl);
     for (int k = 0; k < pl.nsides; ++k) {
       a.sides[k] = pl.sides[k];
       a.r2f[k] = (float)pl.r2[k];
@@ -1468,10 +1487,10 @@ int batch_setup(smre_ctx* c, smre_dtype dt, int n, const smre_batch_image* im,
   D->n = n;
   for (int c2 = 0; c2 < 4; ++c2) {
     int g;
-    if (sizeof(TX) == 8) g = grid_for_batch<double, double, false>(c, B.R, B.SI, B.nitems[c2]);
+    if (sizeof(TX) == 8) g = grid_for_batch<double, double, false>(c, B.R, B.SI, B.nitems[c2], B.stream);
     else if (bp->inc == SMRE_INC_BF16)
-      g = grid_for_batch<float, bf16_t, true>(c, B.R, B.SI, B.nitems[c2]);
-    else g = grid_for_batch<float, float, true>(c, B.R, B.SI, B.nitems[c2]);
+      g = grid_for_batch<float, bf16_t, true>(c, B.R, B.SI, B.nitems[c2], B.stream);
+    else g = grid_for_batch<float, float, true>(c, B.R, B.SI, B.nitems[c2], B.stream);
     if (bp->grid > 0) g = std::min(bp->grid, std::max(1, B.nitems[c2]));
     D->grid[c2] = std::max(1, g);
   }
@@ -1792,11 +1811,9 @@ class HipBackend : public smre_serve::Backend {
     slot_.assign(n_, Slot());
     int occ = 0;
     if (cfg_.inc == SMRE_INC_BF16)
-      HIP_OK(hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &occ, (const void*)region_phase_batch<float, bf16_t, 16, 17, true>, 128, 0));
+      HIP_OK((phase_blocks<float, bf16_t, 16, 17, true>(&occ, false)));
     else
-      HIP_OK(hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &occ, (const void*)region_phase_batch<float, float, 16, 17, true>, 128, 0));
+      HIP_OK((phase_blocks<float, float, 16, 17, true>(&occ, false)));
     hipDeviceProp_t prop;
     HIP_OK(hipGetDeviceProperties(&prop, cfg_.device));
     BatchDev D;
@@ -1868,6 +1885,7 @@ class HipBackend : public smre_serve::Backend {
     a.rtab = (const RoundEntry*)(base + off_roff + sl.plan.meta_rtab);
     a.ld = r.W;
     a.q_byte = (int64_t)at;
+    a.live_off = (int64_t)sl.plan.live_off;
     a.H = r.H;
     a.W = r.W;
     a.nrx = sl.plan.nrx;
@@ -1875,6 +1893,7 @@ class HipBackend : public smre_serve::Backend {
     a.fr = sl.plan.R + sl.plan.smax - 1;
     a.nsides = sl.plan.nsides;
     a.guard = (float)cfg_.guard_rel;
+    a.stream = streams_all(sl.plan);
     for (int k = 0; k < sl.plan.nsides; ++k) {
       a.sides[k] = sl.plan.sides[k];
       a.r2f[k] = (float)sl.plan.r2[k];
