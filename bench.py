@@ -26,27 +26,6 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 FP64_PEAK_TFLOPS = 78.6  # MI355X vector FP64 (256 CUs x 2.4 GHz x 64 lanes x 2 per FMA)
-KERNEL_SRC = os.path.join(ROOT, "paper_1503_03492_amd", "csrc", "kernels.hpp")
-
-
-def measured_traffic(profile):
-    """HBM bytes per launch from the committed counter summary (FETCH_SIZE and
-    WRITE_SIZE, calibrated against a 1 GiB copy), or None when the kernel
-    source has changed since the counters were taken."""
-    import hashlib
-    path = os.path.join(ROOT, "profiles", profile)
-    if not os.path.exists(path):
-        return None
-    sha = hashlib.sha256(open(KERNEL_SRC, "rb").read()).hexdigest()
-    fields = {}
-    for line in open(path):
-        if ":" in line and not line.startswith(("|", "`", "#")):
-            k, v = line.split(":", 1)
-            fields[k.strip()] = v.strip()
-    src = [v for k, v in fields.items() if k.startswith("kernel_source_sha256")]
-    if not src or src[0] != sha or "traffic_bytes_per_launch" not in fields:
-        return None
-    return float(fields["traffic_bytes_per_launch"])
 
 
 def copy_bandwidth(torch, dev, nbytes=1 << 30, reps=5):
@@ -204,6 +183,7 @@ def bench_batch(args):
     el = time.perf_counter() - t0
     wp = sum(r["window_projections"] for rr in reps for r in rr)
     by = sum(r["bytes_moved"] for rr in reps for r in rr)
+    px = sum(8.0 * r["sweeps"] * x.size for rr in reps for r, x in zip(rr, x0s))
     sweeps = [r["sweeps"] for r in reps[-1]]
     kms, nk = reps[-1][0]["kernel_ms"], reps[-1][0]["kernel_launches"]
     out = {"metric": "window projections/s (batched full Dykstra to tol, 64 uneven images)",
@@ -214,14 +194,13 @@ def bench_batch(args):
            "config": {"workload": "batch64_uneven_128-768_sides1-8_fp32", "images": len(x0s),
                       "tol": 1e-5, "region": reps[-1][0]["region"]},
            "sweeps_min_max": [min(sweeps), max(sweeps)],
-           "achieved_GBps_alg": by / el / 1e9,
+           "full_visit_GBps": by / el / 1e9,
            "sweep_graph_ms_avg_sampled": kms / nk if nk else None,
-           # the whole batch's algorithmic bytes (each image's increments and
-           # pixels, read and written once per sweep it runs) over its wall
-           # time, tail included
-           "roofline": {"bound": "hbm", "achieved": by / el / 1e9, "peak": HBM_PEAK_GBS,
-                        "unit": "GB/s", "frac": by / el / 1e9 / HBM_PEAK_GBS, "traffic": None,
-                        "kernel": "region_phase_batch"}}
+           # the images read and written once per sweep over the wall time, tail
+           # included; the sweeps are bound by latency, not by bandwidth
+           "roofline": {"bound": "latency", "achieved": px / el / 1e9, "peak": HBM_PEAK_GBS,
+                        "unit": "GB/s", "frac": px / el / 1e9 / HBM_PEAK_GBS, "traffic": None,
+                        "kernel": "region_phase"}}
     print(json.dumps(out), flush=True)
 
 
@@ -909,11 +888,12 @@ def main():
     sweeps = [r["sweeps"] for r in reps]
     kms = sum(r["kernel_ms"] for r in reps)
     launches = sum(r["kernel_launches"] for r in reps)
-    bytes_alg = sum(r["bytes_moved"] for r in reps)
-    # bytes of one working launch (four per sweep) over the timed launches'
-    # average duration
-    achieved = (bytes_alg / (4 * sum(r["sweeps"] for r in reps))) / (kms / launches * 1e-3) / 1e9 \
-        if kms > 0 and launches > 0 else None
+    # What a sweep cannot do without is the image, read and written once; the
+    # increments of the rounds that do something come on top (a full visit would
+    # move every one: full_visit_bytes_per_sweep).  One launch per sweep.
+    bytes_full = sum(r["bytes_moved"] for r in reps) / max(1, sum(sweeps))
+    bytes_sweep = 2.0 * 4 * H * W
+    achieved = bytes_sweep / (kms / launches * 1e-3) / 1e9 if kms > 0 and launches > 0 else None
     out = {
         "metric": "window projections/s (full Dykstra to tol, 1024^2 image)",
         "value": wp / el,
@@ -937,16 +917,13 @@ def main():
         "sweep_kernel_avg_us": kms / launches * 1e3 if launches else None,
         # against the FP64 oracle's projection of the same float32 input
         "err_vs_oracle": err,
-        "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": achieved / HBM_PEAK_GBS if achieved else None,
-                     "traffic": measured_traffic(wl["profile"]) if "profile" in wl and
-                     args.region in (0, 16) else None,
-                     "kernel": "region_phase",
-                     "copy_gbs_measured": copy_gbs,
-                     "frac_of_copy": achieved / copy_gbs if achieved and copy_gbs else None,
-                     # per working launch: four colour launches per sweep on this image
-                     # (launches queued past convergence exit at once and move nothing)
-                     "bytes_per_launch": bytes_alg / (4 * sum(sweeps)) if sweeps else None},
+        # bound by the chains of dependent rounds of the regions that are active,
+        # not by bandwidth
+        "roofline": {"bound": "latency", "achieved": achieved, "peak": HBM_PEAK_GBS,
+                     "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS if achieved else None,
+                     "traffic": None, "kernel": "region_phase", "copy_gbs_measured": copy_gbs,
+                     "bytes_per_launch": bytes_sweep,
+                     "full_visit_bytes_per_sweep": bytes_full},
     }
     if not args.no_cpu_baseline:
         out["cpu_baseline"] = cpu_baseline(x0.astype(np.float64), sides, r2)

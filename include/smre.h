@@ -126,8 +126,11 @@ typedef struct {
   double max_violation;        /* max_S sum_S x^2 / r2_S - 1 at exit (FP64)     */
   double elapsed_ms;           /* wall time of the call, device-side events     */
   double kernel_ms;            /* sum of sweep-kernel durations (timing on)     */
-  double bytes_moved;          /* algorithmic HBM bytes of the sweeps           */
-  double window_projections;   /* single-window projections performed           */
+  double bytes_moved;          /* bytes of full visits: every increment read and
+                                  written once per sweep (full Dykstra moves fewer:
+                                  it leaves out those that are zero and stay so) */
+  double window_projections;   /* windows settled, one per window and sweep (ICD:
+                                  single-square projections performed)          */
   int64_t kernel_launches;     /* sweep-kernel launches timed                   */
   double pixel_updates;        /* (window, pixel) pairs updated: the sum of the
                                   pixel counts of the projections performed     */

@@ -33,10 +33,17 @@
 // on through LDS counters; every wait is bounded, as in region_job.
 //
 // A side more than half of whose rounds are live is visited round by round
-// without tests (a test costs about as much as a visit); a region more than
-// kDenseNum / kDenseDen of whose rounds are live goes through region_job, which
-// streams whole pages, for kDenseSweeps sweeps, after which a sweep that takes
-// every round for live finds the live ones again.
+// without tests (a test costs about as much as a visit).  A visit takes 1300 to
+// 2000 cycles (0.6 to 0.9 us), a round of region_job, which streams whole pages,
+// 0.38 us; so a region more than about a quarter of whose rounds are live goes
+// through region_job for kDenseSweeps sweeps, after which a sweep that takes every
+// round for live finds the live ones again.
+//
+// Measured, us per sweep with its check, start of this design against now: 512 x 512
+// sides 1..8, 338 against 174 (331 in the first sweep, 156 in the last of 120);
+// 1024 x 1024 sides 1..16, 2550 against 301 (1340, 238).  What bounds it: the chain
+// of visits of the slowest region, and instruction fetch (the code of a side, about
+// 4 KB, runs for a few rounds per job).
 #pragma once
 
 #include "kernels.hpp"
@@ -250,7 +257,7 @@ __device__ __forceinline__ float wave_max16(const float (&v)[16], int lane) {
 // at a time (each pixel of the largest window is read once), so all sides cost
 // one read and one FMA per pixel of the largest.  The sums of 8 sides at a time
 // are taken without a branch between them: with one per side every read waited
-// for the one before (4.4 us for 16 sides).  Leaves by side the mask of the
+// for the one before (16 sides 4.4 us more than one side; 2.8 us now).  Leaves by side the mask of the
 // windows that might exceed the bound (masks are zero before) and the largest
 // sum below it.
 template <typename TX, typename TQ, int R, int SMAX>
