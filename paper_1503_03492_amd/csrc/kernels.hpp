@@ -676,14 +676,20 @@ __device__ __forceinline__ void dispatch_side(const ImageDesc& a, Consumer& c, T
 // only after its previous page has been written back to HBM, and a page is
 // written back (one 16-byte store per lane) once the consumer has finished
 // it.  Full batches of kPrefetch pages run branch-free so the loads stay in
-// flight across batches.
+// flight across batches.  `late`: the consumer may first wait for its pixels, as long
+// as other regions' jobs take, and then raises `begun`; the bounded wait for a page to
+// be finished starts no earlier (the wait for `begun` ends with the consumer's, which
+// is bounded itself).
 template <int MIRROR>
 __device__ __forceinline__ void produce(u32x4* gq, int npg, int64_t stride, u32x4* ring,
-                                        int* ready, const int* consumed, int* abort, int lane) {
+                                        int* ready, const int* consumed, const int* begun,
+                                        bool late, int* abort, int lane) {
   if (npg <= 0) return;
   stride *= 64;  // in 16-byte units
   int cons_seen = 0, wb = 0;
   auto writeback = [&]() {
+    if (late && wb == 0)
+      while (__builtin_amdgcn_readfirstlane(lds_load(begun)) == 0) __builtin_amdgcn_s_sleep(1);
     if (wb >= cons_seen) cons_seen = wait_ge(consumed, wb + 1, abort);
     __asm__ volatile("" ::: "memory");
     const u32x4 v = ring[(wb & (kSlots - 1)) * 64 + lane];
@@ -722,7 +728,7 @@ template <typename TX, typename TQ, int R, int SMAX> struct PhaseLds {
   unsigned char ring[SH::RING];
   TX xs[SH::XSIZE];
   RoundEntry tab[R * R + 2];  // the current side's rounds (+ one readable entry past the end)
-  int ctr[3];  // pages ready, pages consumed, abort flag
+  int ctr[4];  // pages ready, pages consumed, abort flag, pixels read
 };
 
 // One region of one image: two waves of the workgroup enter; the caller
@@ -739,7 +745,8 @@ __device__ __forceinline__ void region_job(const ImageDesc& a, int region, unsig
   const int npg = st.npages;
   if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) != 0) {
     produce<SH::MIRROR>((u32x4*)(q + a.q_byte) + (int64_t)st.first * 64, npg, st.stride,
-                        (u32x4*)L.ring, &L.ctr[0], &L.ctr[1], &L.ctr[2], lane);
+                        (u32x4*)L.ring, &L.ctr[0], &L.ctr[1], &L.ctr[3], shared,
+                        &L.ctr[2], lane);
     return;
   }
 
@@ -748,6 +755,7 @@ __device__ __forceinline__ void region_job(const ImageDesc& a, int region, unsig
   TX* xg = (TX*)a.x;
   TX* xs = L.xs;
   ready();
+  if (shared) lds_store(&L.ctr[3], 1);
   for (int idx = lane; idx < fh * fw; idx += 64) {
     const int i = idx / fw, j = idx - (idx / fw) * fw;
     xs[i * SH::P + j] = load_pixel(xg + (int64_t)(r0 + i) * a.ld + c0 + j, shared);
@@ -812,6 +820,7 @@ __device__ __forceinline__ void reset_counters(PhaseLds<TX, TQ, R, SMAX>& L) {
     L.ctr[0] = 0;
     L.ctr[1] = 0;
     L.ctr[2] = 0;
+    L.ctr[3] = 0;
   }
   __syncthreads();
 }
