@@ -1,5 +1,8 @@
-"""The ways a sweep can visit a region, taken by warm solves through the words their
-workspace holds (the head word of each region's live bits)."""
+"""The ways a sweep can visit a region give the same bits: only the rounds that can
+change something, every round taken for live, whole pages streamed inside the
+one-launch sweep, and the kernel that only streams.  A warm solve is made to take
+one of them through the words its workspace holds (the head word of each region's
+live bits, the last word of the signature)."""
 import pytest
 import torch
 
@@ -24,6 +27,10 @@ def heads(ws, H, W, R, nsides):
     nry, nrx, stride = -(-H // R), -(-W // R), 4 + nsides * R * R // 32
     at = (qbytes - -(-nry * nrx * stride * 4 // 256) * 256) // 4
     return words[at:at + nry * nrx * stride].view(nry, nrx, stride)[:, :, 0]
+
+
+def signature_tail(ws):
+    return ws.view(torch.int64)[(ws.numel() - 256) // 8 + 7:(ws.numel() - 256) // 8 + 8]
 
 
 def first_sweeps(ctx, x0, sides, n, **kw):
@@ -53,6 +60,35 @@ def image(H, W, dtype, seed=1):
     x[:, W // 2:] = 4.0 * x[:, W // 2:] + 3.0
     x[H // 2, W // 5] = 9.0
     return x.to(dtype).cuda()
+
+
+@pytest.mark.parametrize("dtype,inc,kahan", [
+    (torch.float32, smre.INC_SAME, True), (torch.float32, smre.INC_SAME, False),
+    (torch.float32, smre.INC_BF16, True), (torch.float32, smre.INC_BF16, False),
+    (torch.float64, smre.INC_SAME, True)])
+@pytest.mark.parametrize("R,H,W,sides", [
+    (8, 40, 53, list(range(1, 10))), (16, 61, 70, list(range(1, 10))),
+    (16, 64, 95, list(range(1, 17))), (32, 75, 101, [1, 2, 5, 8, 9, 16, 17, 24, 31, 32])])
+def test_every_way_gives_the_same_bits(ctx, dtype, inc, kahan, R, H, W, sides):
+    kw = dict(region=R, inc=inc, kahan=kahan)
+    x0 = image(H, W, dtype)
+    ws = first_sweeps(ctx, x0, sides, 2, **kw)
+    assert int(signature_tail(ws)[0]) == 0
+    got = []
+    for way in ("visit", "all live", "stream", "stream_phase"):
+        w = ws.clone()
+        h = heads(w, H, W, R, len(sides))
+        if way == "visit":
+            h.clamp_(max=ALL_LIVE)  # (the live bits of a region that streamed are stale)
+        elif way == "stream_phase":
+            signature_tail(w)[0] = 1
+        else:
+            h[:] = ALL_LIVE if way == "all live" else STREAM
+        got.append(go_on(ctx, x0, sides, 2, w, **kw))
+        # and once more from what that solve left
+        got.append(go_on(ctx, x0, sides, 1, w, **kw))
+    for i in range(2, len(got)):
+        assert torch.equal(got[i], got[i % 2]), i
 
 
 def test_streamed_region_waits_for_long_jobs_around_it(ctx):
