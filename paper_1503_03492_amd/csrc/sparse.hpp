@@ -1161,10 +1161,6 @@ __global__ __launch_bounds__(kPhaseThreads, sizeof(TX) == 4 && R <= 16 ? 3 : 2) 
     if (it == 0 && threadIdx.x == 0) p.ctrl->ticket[(p.sweep + 1) & 1] = 0;
   }
   while (it < n) {
-    int next = it + gridDim.x;
-    // (the next ticket is taken now, so that its latency passes under the job)
-    if (!items && threadIdx.x == 0)
-      next = atomicAdd(&p.ctrl->ticket[p.sweep & 1], 1);
     int img = 0, region = 0, ry = 0, rx = 0, color = -1;
     const ImageDesc* ap = imgs;
     if (items) {
@@ -1226,9 +1222,15 @@ __global__ __launch_bounds__(kPhaseThreads, sizeof(TX) == 4 && R <= 16 ? 3 : 2) 
     }
     __syncthreads();  // before the next item's set-up
     if (items) {
-      it = next;
+      it += gridDim.x;
     } else {
-      if (threadIdx.x == 0) ticket = next;
+      // (not before the job has ended, though that would hide the atomic's 2 us: the
+      // workgroups that start first would each hold a second region of the first
+      // colour while others already wait for it.  512 x 512, sides 1..8, us per
+      // sweep: all regions streamed 507 with the ticket taken at the job's start,
+      // 347 now; every round taken for live 1390, 780; a call of 60 sweeps on a quiet
+      // image 11.7 ms, 10.1)
+      if (threadIdx.x == 0) ticket = atomicAdd(&p.ctrl->ticket[p.sweep & 1], 1);
       __syncthreads();
       it = __builtin_amdgcn_readfirstlane(ticket);
     }
