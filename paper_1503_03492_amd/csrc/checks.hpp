@@ -282,7 +282,7 @@ __device__ __forceinline__ void ctrl_reset(Ctrl* c) {
   c->delta_key = dkey(0.0);
   c->last_delta = -1.0;
   c->viol_key = dkey(-1.0);
-  c->ticket[0] = c->ticket[1] = c->arrived = c->streamed = 0;
+  c->ticket[0] = c->ticket[1] = c->arrived = c->streams[0] = c->streams[1] = 0;
 }
 
 __global__ void ctrl_reset_kernel(Ctrl* c) { ctrl_reset(c); }

@@ -359,7 +359,7 @@ struct Ctrl {
   unsigned int nf_epoch;         // last ICD call (by its number) whose input was not finite
   int ticket[2];       // next job of a sweep launch: odd and even sweeps
   int arrived;         // check jobs of the sweep that have ended
-  int streamed;        // regions of the sweep streamed whole
+  int streams[2];      // regions that will stream in the sweep after: odd and even sweeps
 };
 
 // ---------------------------------------------------------------- LDS counters

@@ -199,6 +199,7 @@ template <typename TX, typename TQ, int R, int SMAX> struct SparseLds {
   uint32_t now[SMAX * NW];                // and at its end
   __align__(8) int2 odesc[4];             // a round given to the writer: first byte, bytes
   int rounds;                             // of the region, about
+  int head;                               // its head word after the job
   int tested, in_ready, in_done, out_ready, out_done, finished, abort, changed;
 };
 
@@ -941,7 +942,8 @@ __device__ __forceinline__ bool sparse_job(const ImageDesc& a, int region, unsig
     }
     if (lane == 0) {
       L.changed = c.out_seq;
-      lv[0] = 5 * c.nlive > L.rounds + 8 * a.nsides ? kDenseSweeps : 0;
+      L.head = 5 * c.nlive > L.rounds + 8 * a.nsides ? kDenseSweeps : 0;
+      lv[0] = L.head;
     }
     lds_store(&L.finished, 1);
   }
@@ -995,7 +997,8 @@ struct PhaseArgs {
   int* progress;       // by region: last sweep that ended
   void* prev;          // image at the end of the sweep before
   Ctrl* ctrl;
-  int* host_done;      // (host memory) [0] raised with ctrl->done, [1] regions streamed
+  int* host_done;      // (host memory) [0] raised with ctrl->done, [1] ctrl->streams of the
+                       // sweep before
 };
 
 // Waits, with one wave, until the regions of a (2 n + 1)^2 neighbourhood that
@@ -1070,11 +1073,6 @@ __device__ __forceinline__ void sweep_check(const PhaseArgs& p, const ImageDesc&
       c->last_delta = last;
       c->delta_key = dkey(0.0);
       c->arrived = 0;
-      // how many regions the sweep streamed whole
-      __hip_atomic_store(p.host_done + 1,
-                         __hip_atomic_load(&c->streamed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
-                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-      c->streamed = 0;
       if (last < p.tol) {
         c->done_sweep = p.sweep;
         c->done = 1;
@@ -1157,8 +1155,16 @@ __global__ __launch_bounds__(kPhaseThreads, sizeof(TX) == 4 && R <= 16 ? 3 : 2) 
     if (threadIdx.x == 0) ticket = atomicAdd(&p.ctrl->ticket[p.sweep & 1], 1);
     __syncthreads();
     it = __builtin_amdgcn_readfirstlane(ticket);
-    // the counter of the sweep to come, which no launch uses now
-    if (it == 0 && threadIdx.x == 0) p.ctrl->ticket[(p.sweep + 1) & 1] = 0;
+    if (it == 0 && threadIdx.x == 0) {
+      // the counters of the sweep to come, which no launch uses now; first, what
+      // the sweep before counted, for the host
+      const int o = (p.sweep + 1) & 1;
+      __hip_atomic_store(
+          p.host_done + 1,
+          __hip_atomic_load(&p.ctrl->streams[o], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
+          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      p.ctrl->ticket[o] = p.ctrl->streams[o] = 0;
+    }
   }
   while (it < n) {
     int img = 0, region = 0, ry = 0, rx = 0, color = -1;
@@ -1194,9 +1200,10 @@ __global__ __launch_bounds__(kPhaseThreads, sizeof(TX) == 4 && R <= 16 ? 3 : 2) 
           __hip_atomic_store(p.progress + region, p.sweep, __ATOMIC_RELAXED,
                              __HIP_MEMORY_SCOPE_AGENT);
       };
-      int aborted;
+      int aborted, head;
       if (!a.stream && sparse_job<TX, TQ, R, SMAX, KAHAN>(a, region, p.q, lv, L.sparse, shared, ready)) {
         aborted = L.sparse.abort;
+        head = L.sparse.head;
         if (shared) {
           // this wave's pixels have arrived, then every wave's
           __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -1204,18 +1211,16 @@ __global__ __launch_bounds__(kPhaseThreads, sizeof(TX) == 4 && R <= 16 ? 3 : 2) 
           if (threadIdx.x < 64) ended();
         }
       } else {
-        const uint32_t h = a.stream ? 1 : lv[0];
+        head = a.stream ? 0 : (int)lv[0] - 1;
         reset_counters(L.dense);
         if (threadIdx.x < 128)
           region_job<TX, TQ, R, SMAX, KAHAN>(a, region, p.q, L.dense, fresh(threadIdx.x & 63),
                                              shared, ready, ended);
         __syncthreads();
         aborted = L.dense.ctr[2];
-        if (threadIdx.x == 0) {
-          lv[0] = h - 1;
-          if (shared) atomicAdd(&p.ctrl->streamed, 1);
-        }
+        if (threadIdx.x == 0) lv[0] = head;
       }
+      if (shared && head > 1 && threadIdx.x == 0) atomicAdd(&p.ctrl->streams[p.sweep & 1], 1);
       // a wait that gave up (a protocol failure): the host reports a device error
       // for that solve only
       if (threadIdx.x == 0 && aborted) atomicOr((int*)((char*)p.abort + flag), 1);

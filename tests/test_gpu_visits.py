@@ -131,3 +131,30 @@ def test_a_sweep_of_equal_jobs_takes_about_four_of_them(ctx):
             best = min(best, rep["kernel_ms"] * 1e3)
         us.append(best)
     assert us[0] <= 1.3 * us[1], us
+
+
+def solved(ctx, x0, sides, **kw):
+    """The workspace a cold solve leaves, and its report."""
+    o = smre.ProjectOptions(**kw)
+    r2 = smre.chi2_bounds(sides)
+    ws = torch.zeros(ctx.workspace_size(smre.F32, *x0.shape, sides, r2, o), dtype=torch.uint8,
+                     device="cuda")
+    _, rep = ctx.project(x0.clone(), sides, r2, o, workspace=ws)
+    return ws, rep
+
+
+def dense_corner(n, k):
+    g = torch.Generator().manual_seed(3)
+    x = 0.02 * torch.randn(n, n, generator=g, dtype=torch.float64)
+    x[:k, :k] += 40.0 * torch.randn(k, k, generator=g, dtype=torch.float64)
+    return x.float().cuda()
+
+
+@pytest.mark.parametrize("every", [1, 10])
+def test_a_dense_corner_does_not_stream_the_whole_image(ctx, every):
+    # about 16 of 256 regions stream: far from the third at which the solve goes over,
+    # however many sweeps lie between two checks
+    ws, _ = solved(ctx, dense_corner(256, 64), list(range(1, 9)), tol=1e-12, max_sweeps=25,
+                   check_every=every, region=16)
+    assert int((heads(ws, 256, 256, 16, 8) > 1).sum()) > 0
+    assert int(signature_tail(ws)[0]) == 0
