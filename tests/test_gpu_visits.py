@@ -158,3 +158,10 @@ def test_a_dense_corner_does_not_stream_the_whole_image(ctx, every):
                    check_every=every, region=16)
     assert int((heads(ws, 256, 256, 16, 8) > 1).sum()) > 0
     assert int(signature_tail(ws)[0]) == 0
+
+
+@pytest.mark.parametrize("tol,every", [(0, 1), (1e-12, 1), (1e-12, 7)])
+def test_a_dense_image_goes_over_to_streaming(ctx, tol, every):
+    ws, _ = solved(ctx, dense_corner(128, 128), list(range(1, 9)), tol=tol, max_sweeps=20,
+                   check_every=every, region=16)
+    assert int(signature_tail(ws)[0]) == 1
