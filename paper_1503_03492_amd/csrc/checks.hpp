@@ -349,18 +349,23 @@ __global__ __launch_bounds__(256) void delta_batch(const ImageDesc* __restrict__
 }
 
 // One block: close the sweep for every image (check and/or sweep cap) and
-// count the images still running.  counters[0] = sweeps done, [1] = active.
-__global__ __launch_bounds__(256) void decide_batch(BatchCtl* ctl, int n, int check,
-                                                    int* counters) {
-  __shared__ int active;
+// count the images still running.  An image more than a third of whose regions
+// will stream goes over to streaming all of them, for good (see project_impl).
+// counters[0] = sweeps done, [1] = active images, [2] = those that stream.
+__global__ __launch_bounds__(256) void decide_batch(ImageDesc* imgs, BatchCtl* ctl, int n,
+                                                    int check, int* counters) {
+  __shared__ int active, streaming;
   const int sweep = counters[0] + 1;
-  if (threadIdx.x == 0) active = 0;
+  if (threadIdx.x == 0) active = streaming = 0;
   __syncthreads();
   for (int im = threadIdx.x; im < n; im += blockDim.x) {
     BatchCtl& c = ctl[im];
     if (c.done) continue;
     const int sw = ++c.sweeps;
     bool stop = false;
+    if (3 * (int64_t)c.streams > (int64_t)imgs[im].nry * imgs[im].nrx) imgs[im].stream = 1;
+    c.streams = 0;
+    c.stream = imgs[im].stream;
     if (check && sw % c.check_every == 0) {
       const double d = dkey_inv(c.delta_key);
       c.last_delta = d;
@@ -375,12 +380,14 @@ __global__ __launch_bounds__(256) void decide_batch(BatchCtl* ctl, int n, int ch
       c.done_sweep = sw;
     } else {
       atomicAdd(&active, 1);
+      if (c.stream) atomicAdd(&streaming, 1);
     }
   }
   __syncthreads();
   if (threadIdx.x == 0) {
     counters[0] = sweep;
     counters[1] = active;
+    counters[2] = streaming;
   }
 }
 

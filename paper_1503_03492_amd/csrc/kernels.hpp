@@ -434,6 +434,8 @@ struct BatchCtl {
   int check_every;
   int gen;                       // occupant generation (serving: tells a slot's requests apart)
   int aborted;                   // a region job of this image hit a wait bound (device error)
+  int streams;                   // regions that this sweep leaves to stream
+  int stream;                    // the image's descriptor says so: every region streams
   unsigned long long delta_key;  // running max |x - prev| of the checked sweep
   double last_delta;
   double tol;

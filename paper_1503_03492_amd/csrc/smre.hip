@@ -363,7 +363,7 @@ int ensure_ctrl(smre_ctx* c) {
     for (int k = 0; k < 2 * kTimingPairs; ++k) HIP_OK(hipEventCreate(&c->ev[k]));
     HIP_OK(hipEventCreate(&c->t0));
     HIP_OK(hipEventCreate(&c->t1));
-    HIP_OK(hipHostMalloc(&c->counters_host, sizeof(int) * 2 * (kLag + 2), hipHostMallocDefault));
+    HIP_OK(hipHostMalloc(&c->counters_host, sizeof(int) * 4 * (kLag + 2), hipHostMallocDefault));
     HIP_OK(hipStreamCreateWithFlags(&c->capture, hipStreamNonBlocking));
     hipDeviceProp_t prop;
     HIP_OK(hipGetDeviceProperties(&prop, c->device));
@@ -629,6 +629,7 @@ int project_impl(smre_ctx* c, smre_dtype dt, void* x, int64_t H, int64_t W, int6
   int sweep = 0;
   for (sweep = 1; sweep <= p->max_sweeps; ++sweep) {
     l.sweep = sweep;
+    l.streams = &c->ctrl->streams[sweep & 1];
     l.decide = checked(sweep);
     // (the sweep before a checked one keeps the image)
     l.ncheck = l.decide || (sweep < p->max_sweeps && checked(sweep + 1)) ? l.nregions[0] : 0;
@@ -1372,18 +1373,18 @@ struct BatchDev {
   ImageDesc* desc;
   BatchCtl* ctl;
   WorkItem* items[4];
-  int* cnt;       // cnt[0..3] items per colour, cnt[4] sweeps done, cnt[5] active images
+  int* cnt;       // cnt[0..3] items per colour, cnt[4..6] counters of decide_batch
   unsigned char* q;
   void* prev;
-  int grid[4];
+  int grid[2][4];  // of region_phase, of stream_batch
   int n;
   int maxh;
-  bool stream = false;  // stream_batch
 };
 
+// stream: by stream_batch, when every running image streams (decide_batch).
 template <typename TX>
 int enqueue_batch_sweep(smre_dtype dt, const smre_batch_params* bp, int R, int SI,
-                        const BatchDev& D, bool check, hipStream_t s) {
+                        const BatchDev& D, bool check, bool stream, hipStream_t s) {
   const dim3 cg(std::max(1, std::min(64, D.maxh)), D.n);
   if (check)
     hipLaunchKernelGGL((snapshot_batch<TX>), cg, dim3(256), 0, s, D.desc, D.ctl, (TX*)D.prev);
@@ -1394,15 +1395,17 @@ int enqueue_batch_sweep(smre_dtype dt, const smre_batch_params* bp, int R, int S
     l.nitems = D.cnt + color;
     l.done = &D.ctl->done;
     l.abort = &D.ctl->aborted;
+    l.streams = &D.ctl->streams;
     l.flag_stride = sizeof(BatchCtl);
     l.q = D.q;
-    const int rc =
-        launch_phase_any(dt, bp->inc, bp->kahan, R, SI, D.grid[color], l, s, nullptr, D.stream);
+    const int rc = launch_phase_any(dt, bp->inc, bp->kahan, R, SI, D.grid[stream][color], l, s,
+                                    nullptr, stream);
     if (rc) return rc;
   }
   if (check)
     hipLaunchKernelGGL((delta_batch<TX>), cg, dim3(256), 0, s, D.desc, D.ctl, (const TX*)D.prev);
-  hipLaunchKernelGGL(decide_batch, dim3(1), dim3(256), 0, s, D.ctl, D.n, check ? 1 : 0, D.cnt + 4);
+  hipLaunchKernelGGL(decide_batch, dim3(1), dim3(256), 0, s, D.desc, D.ctl, D.n,
+                     check ? 1 : 0, D.cnt + 4);
   HIP_OK(hipGetLastError());
   return SMRE_OK;
 }
@@ -1429,7 +1432,6 @@ int batch_setup(smre_ctx* c, smre_dtype dt, int n, const smre_batch_image* im,
                      B.nitems[0] + B.nitems[1] + B.nitems[2]};
   int64_t fill[4] = {0, 0, 0, 0};
   D->maxh = 1;
-  D->stream = B.stream;
   for (int i = 0; i < n; ++i) {
     const Plan& pl = B.plans[i];
     std::memcpy(meta + B.roff_off[i], pl.meta.data(), pl.meta.size());
@@ -1487,15 +1489,16 @@ int batch_setup(smre_ctx* c, smre_dtype dt, int n, const smre_batch_image* im,
   D->q = ws;
   D->prev = ws + B.off_prev;
   D->n = n;
-  for (int c2 = 0; c2 < 4; ++c2) {
-    int g;
-    if (sizeof(TX) == 8) g = grid_for_batch<double, double, false>(c, B.R, B.SI, B.nitems[c2], B.stream);
-    else if (bp->inc == SMRE_INC_BF16)
-      g = grid_for_batch<float, bf16_t, true>(c, B.R, B.SI, B.nitems[c2], B.stream);
-    else g = grid_for_batch<float, float, true>(c, B.R, B.SI, B.nitems[c2], B.stream);
-    if (bp->grid > 0) g = std::min(bp->grid, std::max(1, B.nitems[c2]));
-    D->grid[c2] = std::max(1, g);
-  }
+  for (int k = 0; k < 2; ++k)
+    for (int c2 = 0; c2 < 4; ++c2) {
+      int g;
+      if (sizeof(TX) == 8) g = grid_for_batch<double, double, false>(c, B.R, B.SI, B.nitems[c2], k);
+      else if (bp->inc == SMRE_INC_BF16)
+        g = grid_for_batch<float, bf16_t, true>(c, B.R, B.SI, B.nitems[c2], k);
+      else g = grid_for_batch<float, float, true>(c, B.R, B.SI, B.nitems[c2], k);
+      if (bp->grid > 0) g = std::min(bp->grid, std::max(1, B.nitems[c2]));
+      D->grid[k][c2] = std::max(1, g);
+    }
   return SMRE_OK;
 }
 
@@ -1592,7 +1595,7 @@ int batch_impl(smre_ctx* c, smre_dtype dt, int n, const smre_batch_image* im,
       hipEvent_t e0 = c->ev[0], e1 = c->ev[1];
       HIP_OK(hipEventRecord(e0, s));
       for (int k = 0; k < 2; ++k) {
-        rc = enqueue_batch_sweep<TX>(dt, bp, Rc, B.SI, D, false, s);
+        rc = enqueue_batch_sweep<TX>(dt, bp, Rc, B.SI, D, false, B.stream, s);
         if (rc) return rc;
       }
       HIP_OK(hipEventRecord(e1, s));
@@ -1617,39 +1620,41 @@ int batch_impl(smre_ctx* c, smre_dtype dt, int n, const smre_batch_image* im,
 
   int max_sw = 0;
   for (int i = 0; i < n; ++i) max_sw = std::max(max_sw, im[i].max_sweeps);
-  // capture one plain and one checking sweep
+  // captured sweeps, each when it is first needed: region_phase, stream_batch
+  if (bp->use_graph) HIP_OK(hipStreamSynchronize(s));
   hipGraphExec_t gx[2] = {nullptr, nullptr};
   hipGraph_t gr[2] = {nullptr, nullptr};
-  if (bp->use_graph) {
-    HIP_OK(hipStreamSynchronize(s));
-    for (int g = 0; g < 2; ++g) {
-      HIP_OK(hipStreamBeginCapture(c->capture, hipStreamCaptureModeThreadLocal));
-      int rc2 = enqueue_batch_sweep<TX>(dt, bp, R, B.SI, D, g == 1, c->capture);
-      hipGraph_t graph = nullptr;
-      HIP_OK(hipStreamEndCapture(c->capture, &graph));
-      if (rc2) return rc2;
-      gr[g] = graph;
-      HIP_OK(hipGraphInstantiate(&gx[g], graph, nullptr, nullptr, 0));
-    }
-  }
+  auto capture = [&](int g) -> int {
+    HIP_OK(hipStreamBeginCapture(c->capture, hipStreamCaptureModeThreadLocal));
+    const int rc2 = enqueue_batch_sweep<TX>(dt, bp, R, B.SI, D, true, g == 1, c->capture);
+    HIP_OK(hipStreamEndCapture(c->capture, &gr[g]));
+    if (rc2) return rc2;
+    HIP_OK(hipGraphInstantiate(&gx[g], gr[g], nullptr, nullptr, 0));
+    return SMRE_OK;
+  };
+  bool stream = B.stream;
   TimingAcc tacc;
   std::deque<std::pair<int, int>> inflight;
   int lag_slot = 0;
   bool host_done = false;
   for (int sweep = 1; sweep <= max_sw && !host_done; ++sweep) {
-    const bool check = true;  // each image tests its own cadence on the device
+    // (each image tests its own cadence on the device)
+    if (bp->use_graph && !gx[stream]) {
+      rc = capture(stream);
+      if (rc) return rc;
+    }
     int slot;
     rc = timing_begin(c, tacc, s, &slot);
     if (rc) return rc;
     if (bp->use_graph) {
-      HIP_OK(hipGraphLaunch(gx[check ? 1 : 0], s));
+      HIP_OK(hipGraphLaunch(gx[stream], s));
     } else {
-      rc = enqueue_batch_sweep<TX>(dt, bp, R, B.SI, D, check, s);
+      rc = enqueue_batch_sweep<TX>(dt, bp, R, B.SI, D, true, stream, s);
       if (rc) return rc;
     }
     rc = timing_end(c, tacc, s, slot);
     if (rc) return rc;
-    HIP_OK(hipMemcpyAsync(c->counters_host + 2 * lag_slot, D.cnt + 4, 2 * sizeof(int),
+    HIP_OK(hipMemcpyAsync(c->counters_host + 4 * lag_slot, D.cnt + 4, 3 * sizeof(int),
                           hipMemcpyDeviceToHost, s));
     HIP_OK(hipEventRecord(c->lag_ev[lag_slot], s));
     inflight.push_back({lag_slot, sweep});
@@ -1658,7 +1663,10 @@ int batch_impl(smre_ctx* c, smre_dtype dt, int n, const smre_batch_image* im,
       auto f = inflight.front();
       inflight.pop_front();
       HIP_OK(hipEventSynchronize(c->lag_ev[f.first]));
-      if (c->counters_host[2 * f.first + 1] == 0) host_done = true;
+      const int* seen = c->counters_host + 4 * f.first;
+      if (seen[1] == 0) host_done = true;
+      // (images that stream do so to their end, and none joins)
+      if (seen[2] == seen[1]) stream = true;
     }
   }
   HIP_OK(hipStreamSynchronize(s));
@@ -1709,9 +1717,9 @@ int batch_impl(smre_ctx* c, smre_dtype dt, int n, const smre_batch_image* im,
 // HIP backend of the continuous-batching server (scheduler: serve_core.hpp).
 // One device arena holds every admitted request's image, snapshot, region
 // table and increments; descriptors and control blocks sit in fixed slot
-// tables, so a single captured graph (snapshot, four persistent colour
-// launches over the current work lists, delta, decide) serves every sweep
-// whatever the mix.  Requests join between sweeps; a finished request is
+// tables, so a captured graph (snapshot, four persistent colour launches
+// over the current work lists, delta, decide) serves every sweep whatever the
+// mix; a second one, of stream_batch, when every admitted request streams.  Requests join between sweeps; a finished request is
 // retired one sweep after its flag is set (its items are skipped meanwhile).
 class Arena {
  public:
@@ -1756,8 +1764,10 @@ class HipBackend : public smre_serve::Backend {
   ~HipBackend() override {
     (void)hipSetDevice(cfg_.device);
     if (stream_) (void)hipStreamSynchronize(stream_);
-    if (gx_) (void)hipGraphExecDestroy(gx_);
-    if (graph_) (void)hipGraphDestroy(graph_);
+    for (int k = 0; k < 2; ++k) {
+      if (gx_[k]) (void)hipGraphExecDestroy(gx_[k]);
+      if (graph_[k]) (void)hipGraphDestroy(graph_[k]);
+    }
     if (arena_) (void)hipFree(arena_);
     if (tables_) (void)hipFree(tables_);
     if (hctl_) (void)hipHostFree(hctl_);
@@ -1811,19 +1821,21 @@ class HipBackend : public smre_serve::Backend {
     HIP_OK(hipMemcpy(ctl_, c0.data(), sizeof(BatchCtl) * n_, hipMemcpyHostToDevice));
     HIP_OK(hipMemset(cnt_, 0, 64));
     slot_.assign(n_, Slot());
-    int occ = 0;
-    if (cfg_.inc == SMRE_INC_BF16)
-      HIP_OK((phase_blocks<float, bf16_t, 16, 17, true>(&occ, false)));
-    else
-      HIP_OK((phase_blocks<float, float, 16, 17, true>(&occ, false)));
     hipDeviceProp_t prop;
     HIP_OK(hipGetDeviceProperties(&prop, cfg_.device));
     BatchDev D;
     D.desc = desc_;
     D.ctl = ctl_;
-    for (int c = 0; c < 4; ++c) {
-      D.items[c] = items_[c];
-      D.grid[c] = std::max(1, occ) * prop.multiProcessorCount;
+    for (int k = 0; k < 2; ++k) {
+      int occ = 0;
+      if (cfg_.inc == SMRE_INC_BF16)
+        HIP_OK((phase_blocks<float, bf16_t, 16, 17, true>(&occ, k)));
+      else
+        HIP_OK((phase_blocks<float, float, 16, 17, true>(&occ, k)));
+      for (int c = 0; c < 4; ++c) {
+        D.items[c] = items_[c];
+        D.grid[k][c] = std::max(1, occ) * prop.multiProcessorCount;
+      }
     }
     D.cnt = cnt_;
     D.q = (unsigned char*)arena_;
@@ -1836,11 +1848,13 @@ class HipBackend : public smre_serve::Backend {
     bp.kahan = cfg_.kahan;
     bp.check_every = 1;
     bp.guard_rel = cfg_.guard_rel;
-    HIP_OK(hipStreamBeginCapture(stream_, hipStreamCaptureModeThreadLocal));
-    const int rc = enqueue_batch_sweep<float>(SMRE_F32, &bp, 16, 17, D, true, stream_);
-    HIP_OK(hipStreamEndCapture(stream_, &graph_));
-    if (rc) return rc;
-    HIP_OK(hipGraphInstantiate(&gx_, graph_, nullptr, nullptr, 0));
+    for (int k = 0; k < 2; ++k) {
+      HIP_OK(hipStreamBeginCapture(stream_, hipStreamCaptureModeThreadLocal));
+      const int rc = enqueue_batch_sweep<float>(SMRE_F32, &bp, 16, 17, D, true, k == 1, stream_);
+      HIP_OK(hipStreamEndCapture(stream_, &graph_[k]));
+      if (rc) return rc;
+      HIP_OK(hipGraphInstantiate(&gx_[k], graph_[k], nullptr, nullptr, 0));
+    }
     return SMRE_OK;
   }
 
@@ -1914,7 +1928,7 @@ class HipBackend : public smre_serve::Backend {
     HIP_OK(hipMemcpyAsync(ctl_ + s, &sl.ctl, sizeof(BatchCtl), hipMemcpyHostToDevice, stream_));
     HIP_OK(hipStreamSynchronize(stream_));  // host staging (r.in, plan, desc) released safely
     sl.active = true;
-    sl.reported = false;
+    sl.reported = sl.stream = false;
     sl.t_admit = smre_serve::now_s();
     dirty_ = true;
     return SMRE_OK;
@@ -1926,7 +1940,10 @@ class HipBackend : public smre_serve::Backend {
       int rc = upload_lists();
       if (rc) return rc;
     }
-    HIP_OK(hipGraphLaunch(gx_, stream_));
+    // (an image that streams does so to its end)
+    bool stream = true;
+    for (const Slot& sl : slot_) stream = stream && (!sl.active || sl.reported || sl.stream);
+    HIP_OK(hipGraphLaunch(gx_[stream], stream_));
     const int k = parity_;
     HIP_OK(hipMemcpyAsync(hctl_ + k * n_, ctl_, sizeof(BatchCtl) * n_, hipMemcpyDeviceToHost,
                           stream_));
@@ -1938,8 +1955,10 @@ class HipBackend : public smre_serve::Backend {
       HIP_OK(hipEventSynchronize(ev_[pk]));
       for (int i = 0; i < n_; ++i) {
         Slot& sl = slot_[i];
-        if (sl.active && !sl.reported && sl.finished_in(hctl_[pk * n_ + i])) {
-          sl.last = hctl_[pk * n_ + i];
+        const BatchCtl& c = hctl_[pk * n_ + i];
+        if (c.gen == sl.ctl.gen && c.stream) sl.stream = true;
+        if (sl.active && !sl.reported && sl.finished_in(c)) {
+          sl.last = c;
           sl.reported = true;
           fin.push_back(i);
         }
@@ -1991,6 +2010,7 @@ class HipBackend : public smre_serve::Backend {
   static constexpr int kCapItems = 1 << 18;
   struct Slot {
     bool active = false, reported = false;
+    bool stream = false;  // its control block said so
     size_t off = 0, size = 0;
     Plan plan;
     ImageDesc desc;
@@ -2075,8 +2095,8 @@ class HipBackend : public smre_serve::Backend {
   bool have_prev_ = false;
   bool dirty_ = false;
   int generation_ = 0;
-  hipGraph_t graph_ = nullptr;
-  hipGraphExec_t gx_ = nullptr;
+  hipGraph_t graph_[2] = {};  // a sweep by region_phase, by stream_batch
+  hipGraphExec_t gx_[2] = {};
   std::vector<Slot> slot_;
 };
 

@@ -966,8 +966,8 @@ __device__ __forceinline__ bool sparse_job(const ImageDesc& a, int region, unsig
 // ---------------------------------------------------------------- sweep kernel
 // Two uses.
 //
-// A batch, one colour per launch: work item `it` is items[it]; done / abort are the
-// flags of image i at byte i * flag_stride.
+// A batch, one colour per launch: work item `it` is items[it]; done / abort / streams
+// are those of image i at byte i * flag_stride.
 //
 // One image, a whole sweep per launch (items null): the jobs of the sweep are its
 // regions colour by colour, then, in a sweep that is checked, its check jobs
@@ -986,6 +986,7 @@ struct PhaseArgs {
   const int* nitems;
   const int* done;
   int* abort;
+  int* streams;        // count of regions that will stream in the sweep after
   int64_t flag_stride;
   unsigned char* q;
   // one image
@@ -1220,7 +1221,7 @@ __global__ __launch_bounds__(kPhaseThreads, sizeof(TX) == 4 && R <= 16 ? 3 : 2) 
         aborted = L.dense.ctr[2];
         if (threadIdx.x == 0) lv[0] = head;
       }
-      if (shared && head > 1 && threadIdx.x == 0) atomicAdd(&p.ctrl->streams[p.sweep & 1], 1);
+      if (head > 1 && threadIdx.x == 0) atomicAdd((int*)((char*)p.streams + flag), 1);
       // a wait that gave up (a protocol failure): the host reports a device error
       // for that solve only
       if (threadIdx.x == 0 && aborted) atomicOr((int*)((char*)p.abort + flag), 1);
