@@ -620,7 +620,8 @@ int project_impl(smre_ctx* c, smre_dtype dt, void* x, int64_t H, int64_t W, int6
   l.ctrl = c->ctrl;
   l.host_done = c->counters_host;
   c->counters_host[0] = c->counters_host[1] = 0;
-  // sig[7]: the increments kept for a warm start have no live bits
+  // sig[7]: a warm start from the increments kept has to stream (they may have no
+  // live bits)
   bool stream = streams_all(pl) || (p->warm && have[7] != 0);
   // as many workgroups as a colour has regions, at most what the device holds
   // (further ones would only find the tickets taken)
@@ -656,7 +657,7 @@ int project_impl(smre_ctx* c, smre_dtype dt, void* x, int64_t H, int64_t W, int6
       // many regions stream: the leaner kernel is faster at that, and what it
       // leaves out (the live bits) is not needed again in this problem (256 x 256
       // grey levels, 3 x 40 sweeps: 40 against 55 ms)
-      if (!stream && 3 * seen[1] > nreg) stream = true;
+      if (!stream && 3 * (int64_t)seen[1] > nreg) stream = true;
       HIP_OK(hipEventRecord(c->lag_ev[e], s));
     }
   }
@@ -670,7 +671,8 @@ int project_impl(smre_ctx* c, smre_dtype dt, void* x, int64_t H, int64_t W, int6
   HIP_OK(hipMemcpy(c->ctrl_host, c->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost));
   const Ctrl fin = *c->ctrl_host;
   const int sweeps_run = fin.done ? fin.done_sweep : p->max_sweeps;
-  sig[7] = stream;
+  // what is kept goes on by streaming if this solve did, or would have before long
+  sig[7] = stream || 3 * (int64_t)fin.streams[sweeps_run & 1] > nreg;
   if (!fin.abort)  // the increments belong to this problem now
     HIP_OK(hipMemcpy(dsig, sig, sizeof sig, hipMemcpyHostToDevice));
   double viol = 0.0;
