@@ -47,6 +47,7 @@
 #pragma once
 
 #include "kernels.hpp"
+#include "growth.hpp"
 
 namespace smre {
 
@@ -330,7 +331,7 @@ struct Sparse {
   int in_seq, in_seen, in_off;     // live rounds taken from the ring, loaded; next slot
   int out_seq, out_seen, out_off;  // rounds given to the writer, written; next slot
   int nlive;       // rounds live at the end
-  float grown;     // lane's part of the growth of x^2 summed over pixels since test_all
+  Growth grown;    // lane's part of the growth of x^2 summed over pixels
 };
 
 // Test of every window of side S against its bound, from the footprint: the
@@ -403,11 +404,9 @@ __device__ __forceinline__ uint32_t flagged_rounds(SparseLds<TX, TQ, R, SMAX>& L
   return lane < SL::NW ? L.need[lane] : 0;
 }
 
-constexpr float kGrowth = 1.001f;  // covers the rounding of the growth sums
-
 // One side of a region that holds live rounds or windows that might exceed their
-// bound: see the head of this file.  grown: growth since test_all, slack: what
-// the windows below the bound had left of it then.
+// bound: see the head of this file.  grown: growth from test_all to this side,
+// slack: what the windows below the bound had left of it then.
 template <typename TX, typename TQ, int R, int SMAX, int S, bool KAHAN>
 __device__ __forceinline__ void sparse_side(Sparse& c, SparseLds<TX, TQ, R, SMAX>& L, int k,
                                             int qb0, float thr, float grown, float slack) {
@@ -436,9 +435,9 @@ __device__ __forceinline__ void sparse_side(Sparse& c, SparseLds<TX, TQ, R, SMAX
     if (__builtin_amdgcn_readfirstlane(L.flag[S]))
       cand |= flagged_rounds<TX, TQ, R, SMAX, S>(L, lane);
   }
-  // Growth up to which no window is lifted to its bound, lane's part: a lane
-  // holds at least a 64th of the sum if the sum passes the slack.
-  float base = 0.0f, limit = slack * (1.0f / (64.0f * kGrowth));
+  // Growth up to which no window is lifted to its bound (what is left of the slack),
+  // and a lane's part of it: a lane holds at least a 64th of a sum that passes it.
+  float rest = slack - grown * kGrowth, limit = rest * (1.0f / (64.0f * kGrowth));
 
   const int wl = lane / G, jj = lane % G;
   const int bry = wl / BC, brx = wl % BC, jr = jj / GC, jc = jj % GC;
@@ -461,9 +460,9 @@ __device__ __forceinline__ void sparse_side(Sparse& c, SparseLds<TX, TQ, R, SMAX
       if (blk >= 0) later = lane < l ? 0u : lane > l ? later : later & (~1u << b);
       float top;
       cand = (livew | window_test<TX, TQ, R, SMAX, S>(L, lane, rhi, chi, thr, &top)) & later;
-      slack = thr - top;
-      base = c.grown;
-      limit = base + slack * (1.0f / (64.0f * kGrowth));
+      c.grown.tested();
+      rest = thr - top;
+      limit = rest * (1.0f / (64.0f * kGrowth));
       test = false;
     }
     const uint64_t mw = __ballot(cand != 0);
@@ -561,7 +560,7 @@ __device__ __forceinline__ void sparse_side(Sparse& c, SparseLds<TX, TQ, R, SMAX
             const float d = (float)((xn - xv[u][v]) * (xn + xv[u][v]));
             e += !keep || d <= 0.0f ? 0.0f : d;
           }
-        c.grown += valid ? e : 0.0f;
+        c.grown.add(valid ? e : 0.0f);
         L.odesc[c.out_seq & 3] = int2{start, nbr * nbc * (S * S * ES)};
         lds_store(&L.out_ready, ++c.out_seq);
         lds_store(&L.in_done, c.in_seq);
@@ -573,8 +572,8 @@ __device__ __forceinline__ void sparse_side(Sparse& c, SparseLds<TX, TQ, R, SMAX
         // Another test if the growth may have lifted a window to its bound, or
         // if the round became live and others that are not live remain, which
         // what it took away may have brought below the bound.
-        if (__builtin_expect(__ballot(!(c.grown < limit)) != 0, 0))
-          test = !(group_sum<64>(c.grown - base) * kGrowth < slack);
+        if (__builtin_expect(__ballot(!(c.grown.since < limit)) != 0, 0))
+          test = !(group_sum<64>(c.grown.since) * kGrowth < rest);
         if (live_out && !live_in && ((m & ~livem) != 0 || __ballot((cand & ~livew) != 0) != 0)) test = true;
         if (test) break;
       }
@@ -906,7 +905,7 @@ __device__ __forceinline__ bool sparse_job(const ImageDesc& a, int region, unsig
     c.lane = lane;
     c.in_seq = c.in_seen = c.in_off = c.out_seq = c.out_seen = c.out_off = 0;
     c.nlive = 0;
-    c.grown = 0.0f;
+    c.grown = {0.0f, 0.0f, 0.0f};
     wait_ge(&L.tested, 2, &L.abort, kSparseSpin);
     __asm__ volatile("" ::: "memory");
     // lane: side
@@ -938,7 +937,8 @@ __device__ __forceinline__ bool sparse_job(const ImageDesc& a, int region, unsig
       SMRE_SIDE_SWITCH(side, SMRE_CASE)
 #undef SMRE_CASE
       __asm__ volatile("" ::: "memory");
-      grown = group_sum<64>(c.grown);
+      c.grown.side_done();
+      grown = group_sum<64>(c.grown.total);
     }
     if (lane == 0) {
       L.changed = c.out_seq;
