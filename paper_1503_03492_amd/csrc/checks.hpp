@@ -59,15 +59,79 @@ __global__ void decide_kernel(Ctrl* ctrl, double tol, int sweep) {
 __global__ void nonfinite_reset_kernel(Ctrl* ctrl) { ctrl->nonfinite = 0; }
 
 template <typename TX>
-__global__ __launch_bounds__(256) void nonfinite_kernel(const TX* x, int64_t ld, int H, int W,
-                                                        Ctrl* ctrl) {
+__device__ __forceinline__ void nonfinite_rows(const TX* x, int64_t ld, int H, int W, int first,
+                                               int step, Ctrl* ctrl) {
   int bad = 0;
-  for (int r = blockIdx.x; r < H; r += gridDim.x)
+  for (int r = first; r < H; r += step)
     for (int col = threadIdx.x; col < W; col += blockDim.x) {
       const double v = (double)x[(int64_t)r * ld + col];
       bad |= !(v - v == 0.0);
     }
   if (__any(bad) && (threadIdx.x & 63) == 0) atomicOr(&ctrl->nonfinite, 1);
+}
+
+template <typename TX>
+__global__ __launch_bounds__(256) void nonfinite_kernel(const TX* x, int64_t ld, int H, int W,
+                                                        Ctrl* ctrl) {
+  nonfinite_rows(x, ld, H, W, blockIdx.x, gridDim.x, ctrl);
+}
+
+// The input of a full Dykstra solve: the same test, and, by the first `tiles` blocks,
+// how many windows are far over their bound, in up to kFarTiles tiles of 16 x 16
+// anchors spread over the image: enough to tell a solve that will stream
+// (starts_streaming in smre.hip).
+constexpr int kFarTiles = 64;
+struct FarTest {
+  int tiles, smax;
+  float lim[33];  // by side: 4 r2, or 0 if the side is not projected
+};
+template <typename TX>
+__global__ __launch_bounds__(256) void input_kernel(const TX* x, int64_t ld, int H, int W,
+                                                    FarTest t, Ctrl* ctrl) {
+  if ((int)blockIdx.x >= t.tiles) {
+    nonfinite_rows(x, ld, H, W, blockIdx.x - t.tiles, gridDim.x - t.tiles, ctrl);
+    return;
+  }
+  constexpr int P = 16 + 32 - 1;
+  __shared__ float px[P * P];
+  const int ntx = (W + 15) / 16;
+  const uint64_t nt = (uint64_t)ntx * ((H + 15) / 16);
+  // (multiples of the golden ratio, modulo 1: evenly spread, on every column of tiles)
+  const uint32_t frac = blockIdx.x * 2654435769u;
+  const int at = t.tiles < kFarTiles ? (int)blockIdx.x : (int)((frac * nt) >> 32);
+  const int r0 = at / ntx * 16, c0 = at % ntx * 16, n = 16 + t.smax - 1;
+  // (all of a thread's loads issued before the first is used)
+  constexpr int NL = (P + 3) / 4;
+  const int lr = threadIdx.x / 64, lc = threadIdx.x % 64;
+  float v[NL];
+#pragma unroll
+  for (int u = 0; u < NL; ++u) {
+    const int r = lr + 4 * u;
+    v[u] = r < n && lc < n && r0 + r < H && c0 + lc < W
+               ? (float)x[(int64_t)(r0 + r) * ld + c0 + lc] : 0.0f;
+  }
+#pragma unroll
+  for (int u = 0; u < NL; ++u)
+    if (lr + 4 * u < n && lc < n) px[(lr + 4 * u) * P + lc] = v[u];
+  __syncthreads();
+  const int i = threadIdx.x / 16, j = threadIdx.x % 16;
+  const int fit = min(H - r0 - i, W - c0 - j);
+  const float* p = px + i * P + j;
+  // a window grows by a column and a row
+  float col = 0.0f, row = 0.0f;
+  int over = 0, all = 0;
+  for (int s = 1; s <= t.smax; ++s) {
+#pragma unroll 4
+    for (int l = 0; l < s; ++l) {
+      const float a = p[l * P + s - 1], b = l < s - 1 ? p[(s - 1) * P + l] : 0.0f;
+      col = __builtin_fmaf(a, a, col);
+      row = __builtin_fmaf(b, b, row);
+    }
+    const bool is = t.lim[s] > 0.0f && s <= fit;
+    all += __popcll(__ballot(is));
+    over += __popcll(__ballot(is && col + row > t.lim[s]));
+  }
+  if ((threadIdx.x & 63) == 0) atomicAdd(&ctrl->far, (unsigned long long)over << 32 | (unsigned)all);
 }
 
 // Feasibility: max over windows S of the requested sides of sum_S x^2 / r2_s - 1,
@@ -283,6 +347,7 @@ __device__ __forceinline__ void ctrl_reset(Ctrl* c) {
   c->last_delta = -1.0;
   c->viol_key = dkey(-1.0);
   c->ticket[0] = c->ticket[1] = c->arrived = c->streams[0] = c->streams[1] = 0;
+  c->far = 0;
 }
 
 __global__ void ctrl_reset_kernel(Ctrl* c) { ctrl_reset(c); }

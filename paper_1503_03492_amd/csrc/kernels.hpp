@@ -360,6 +360,7 @@ struct Ctrl {
   int ticket[2];       // next job of a sweep launch: odd and even sweeps
   int arrived;         // check jobs of the sweep that have ended
   int streams[2];      // regions that will stream in the sweep after: odd and even sweeps
+  unsigned long long far;  // input's sampled windows: low half all, high half far over
 };
 
 // ---------------------------------------------------------------- LDS counters

@@ -428,13 +428,21 @@ template <typename TX> void launch_check(int R, const PhaseArgs& p, hipStream_t 
 // 15.6 ms for 200 sweeps; 219 x 536, sides 1, 2, 4, 8, 88 rounds: 4.5 against 5.2 ms
 // for 35; 467 x 213, sides 1..7, 175 rounds: 6.3 against 4.7 ms for 23).
 constexpr int kStreamRounds = 100;
-int streams_all(const Plan& pl) {
+int region_rounds(int R, int n, const int* sides) {
   int rounds = 0;
-  for (int k = 0; k < pl.nsides; ++k) {
-    const int n = axis_rounds(pl.R, pl.sides[k]);
-    rounds += n * n;
-  }
-  return rounds <= kStreamRounds;
+  for (int k = 0; k < n; ++k) rounds += axis_rounds(R, sides[k]) * axis_rounds(R, sides[k]);
+  return rounds;
+}
+int region_rounds(const Plan& pl) { return region_rounds(pl.R, pl.nsides, pl.sides); }
+bool streams_all(const Plan& pl) { return region_rounds(pl) <= kStreamRounds; }
+
+// A cold solve streams from its first sweep if its input is dense and its regions
+// have few rounds: `far` (input_kernel) says more than 3 of 4 sampled windows hold more
+// than four times their bound.
+constexpr int kFewRounds = 256;
+bool starts_streaming(const Plan& pl, uint64_t far) {
+  return streams_all(pl) ||
+         (region_rounds(pl) <= kFewRounds && 4 * (far >> 32) > 3 * (far & 0xFFFFFFFFu));
 }
 
 // Feasibility of frames stacked fstride elements apart over the sides (each
@@ -536,6 +544,28 @@ int check_nonfinite(smre_ctx* c, const void* x, int64_t H, int64_t W, int64_t ld
   return SMRE_OK;
 }
 
+// The input test of a full Dykstra solve that has been planned (its sides and bounds
+// are in range), with the control block reset.  far: for starts_streaming, or null.
+template <typename TX>
+int check_input(smre_ctx* c, const void* x, int64_t H, int64_t W, int64_t ld, int n_sides,
+                const int32_t* sides, const double* radius2, hipStream_t s, bool* bad,
+                uint64_t* far) {
+  FarTest t{};
+  for (int k = 0; k < n_sides && far; ++k) {
+    t.smax = std::max(t.smax, (int)sides[k]);
+    t.lim[sides[k]] = (float)(4.0 * radius2[k]);
+  }
+  if (far) t.tiles = (int)std::min<int64_t>(kFarTiles, ((H + 15) / 16) * ((W + 15) / 16));
+  hipLaunchKernelGGL((input_kernel<TX>), dim3(t.tiles + grid_rows(H)), dim3(256), 0, s,
+                     (const TX*)x, ld, (int)H, (int)W, t, c->ctrl);
+  HIP_OK(hipGetLastError());
+  HIP_OK(hipMemcpyAsync(c->ctrl_host, c->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s));
+  HIP_OK(hipStreamSynchronize(s));
+  *bad = c->ctrl_host->nonfinite != 0;
+  if (far) *far = c->ctrl_host->far;
+  return SMRE_OK;
+}
+
 template <typename TX>
 int project_impl(smre_ctx* c, smre_dtype dt, void* x, int64_t H, int64_t W, int64_t ld,
                  const smre_params* p, Plan& pl, unsigned char* ws, hipStream_t s,
@@ -544,7 +574,10 @@ int project_impl(smre_ctx* c, smre_dtype dt, void* x, int64_t H, int64_t W, int6
   HIP_OK(hipEventRecord(c->t0, s));
   hipLaunchKernelGGL(ctrl_reset_kernel, dim3(1), dim3(1), 0, s, c->ctrl);
   bool bad = false;
-  int rc = check_nonfinite<TX>(c, x, H, W, ld, s, &bad);
+  uint64_t far = 0;
+  const bool few = !p->warm && !streams_all(pl) && region_rounds(pl) <= kFewRounds;
+  int rc = check_input<TX>(c, x, H, W, ld, p->n_sides, p->sides, p->radius2, s, &bad,
+                           few ? &far : nullptr);
   if (rc) return rc;
   if (bad) return SMRE_ENONFINITE;
 
@@ -622,7 +655,7 @@ int project_impl(smre_ctx* c, smre_dtype dt, void* x, int64_t H, int64_t W, int6
   c->counters_host[0] = c->counters_host[1] = 0;
   // sig[7]: a warm start from the increments kept has to stream (they may have no
   // live bits)
-  bool stream = streams_all(pl) || (p->warm && have[7] != 0);
+  bool stream = p->warm ? streams_all(pl) || have[7] != 0 : starts_streaming(pl, far);
   // as many workgroups as a colour has regions, at most what the device holds
   // (further ones would only find the tickets taken)
   const int grid = std::max(1, std::min(l.nregions[0], 4 * c->cus));
@@ -1286,7 +1319,6 @@ struct BatchPlan {
   int R = 16;
   int SI = 17;  // kernel instance shared by every image (instance_smax of the batch)
   int n = 0;
-  bool stream = true;  // every image's regions are streamed whole (streams_all)
   std::vector<Plan> plans;
   std::vector<size_t> qoff;       // byte offset of each image's increments
   std::vector<size_t> roff_off;   // byte offset of each image's metadata blob
@@ -1306,7 +1338,6 @@ int plan_batch(smre_dtype dt, int n, const smre_batch_image* im, const smre_batc
     for (int k = 0; k < im[i].n_sides && im[i].sides; ++k)
       smax_all = std::max(smax_all, (int)im[i].sides[k]);
   B->SI = instance_smax(R, smax_all);
-  B->stream = true;
   B->plans.assign(n, Plan());
   B->qoff.assign(n, 0);
   B->roff_off.assign(n, 0);
@@ -1330,7 +1361,6 @@ int plan_batch(smre_dtype dt, int n, const smre_batch_image* im, const smre_batc
     if (!im[i].x || im[i].ld < im[i].W) return SMRE_EINVAL;
     int rc = plan_project(dt, im[i].H, im[i].W, &p, &B->plans[i], need_offsets, B->SI);
     if (rc) return rc;
-    B->stream = B->stream && streams_all(B->plans[i]);
     B->qoff[i] = B->qbytes;
     B->qbytes += align_up(B->plans[i].qbytes, kPage);
     B->roff_off[i] = B->roff_elems;
@@ -1381,6 +1411,7 @@ struct BatchDev {
   int grid[2][4];  // of region_phase, of stream_batch
   int n;
   int maxh;
+  bool stream;  // every image streams from the first sweep
 };
 
 // stream: by stream_batch, when every running image streams (decide_batch).
@@ -1416,8 +1447,8 @@ int enqueue_batch_sweep(smre_dtype dt, const smre_batch_params* bp, int R, int S
 // the increments.  Host staging lives in `host` until the stream is synced.
 template <typename TX>
 int batch_setup(smre_ctx* c, smre_dtype dt, int n, const smre_batch_image* im,
-                const smre_batch_params* bp, const BatchPlan& B, unsigned char* ws,
-                std::vector<unsigned char>& host, BatchDev* D, hipStream_t s) {
+                const smre_batch_params* bp, const BatchPlan& B, const std::vector<uint64_t>& far,
+                unsigned char* ws, std::vector<unsigned char>& host, BatchDev* D, hipStream_t s) {
   (void)c;
   const size_t es = (bp->inc == SMRE_INC_BF16) ? 2 : sizeof(TX);
   (void)es;
@@ -1434,6 +1465,7 @@ int batch_setup(smre_ctx* c, smre_dtype dt, int n, const smre_batch_image* im,
                      B.nitems[0] + B.nitems[1] + B.nitems[2]};
   int64_t fill[4] = {0, 0, 0, 0};
   D->maxh = 1;
+  D->stream = true;
   for (int i = 0; i < n; ++i) {
     const Plan& pl = B.plans[i];
     std::memcpy(meta + B.roff_off[i], pl.meta.data(), pl.meta.size());
@@ -1451,7 +1483,8 @@ int batch_setup(smre_ctx* c, smre_dtype dt, int n, const smre_batch_image* im,
     a.fr = pl.R + pl.smax - 1;
     a.nsides = pl.nsides;
     a.guard = (float)bp->guard_rel;
-    a.stream = streams_all(pl);
+    a.stream = starts_streaming(pl, far[i]);
+    D->stream = D->stream && a.stream;
     for (int k = 0; k < pl.nsides; ++k) {
       a.sides[k] = pl.sides[k];
       a.r2f[k] = (float)pl.r2[k];
@@ -1554,16 +1587,21 @@ int batch_impl(smre_ctx* c, smre_dtype dt, int n, const smre_batch_image* im,
   int rc = batch_validate(dt, n, im, bp, &smax);
   if (rc) return rc;
   // input check
+  std::vector<uint64_t> far(n, 0);
+  const std::vector<int> cands = region_candidates(smax, bp->region);
   for (int i = 0; i < n; ++i) {
+    bool few = false;
+    for (int Rc : cands)
+      few = few || region_rounds(Rc, im[i].n_sides, im[i].sides) <= kFewRounds;
     hipLaunchKernelGGL(ctrl_reset_kernel, dim3(1), dim3(1), 0, s, c->ctrl);
     bool bad = false;
-    rc = check_nonfinite<TX>(c, im[i].x, im[i].H, im[i].W, im[i].ld, s, &bad);
+    rc = check_input<TX>(c, im[i].x, im[i].H, im[i].W, im[i].ld, im[i].n_sides, im[i].sides,
+                         im[i].radius2, s, &bad, few ? &far[i] : nullptr);
     if (rc) return rc;
     if (bad) return SMRE_ENONFINITE;
   }
   HIP_OK(hipEventRecord(c->t0, s));
   // region side: requested, cached, or tuned on a scratch run of two sweeps
-  std::vector<int> cands = region_candidates(smax, bp->region);
   char keyb[160];
   snprintf(keyb, sizeof keyb, "dt%d inc%d k%d smax%d n%d", (int)dt, bp->inc, bp->kahan, smax, n);
   std::string key(keyb);
@@ -1591,13 +1629,13 @@ int batch_impl(smre_ctx* c, smre_dtype dt, int n, const smre_batch_image* im,
       for (int i = 0; i < n; ++i)
         HIP_OK(hipMemcpy2DAsync(saved[i], im[i].W * sizeof(TX), im[i].x, im[i].ld * sizeof(TX),
                                 im[i].W * sizeof(TX), im[i].H, hipMemcpyDeviceToDevice, s));
-      rc = batch_setup<TX>(c, dt, n, im, bp, B, ws, host, &D, s);
+      rc = batch_setup<TX>(c, dt, n, im, bp, B, far, ws, host, &D, s);
       if (rc) return rc;
       // the snapshot buffer holds the saved inputs: sweep without checks
       hipEvent_t e0 = c->ev[0], e1 = c->ev[1];
       HIP_OK(hipEventRecord(e0, s));
       for (int k = 0; k < 2; ++k) {
-        rc = enqueue_batch_sweep<TX>(dt, bp, Rc, B.SI, D, false, B.stream, s);
+        rc = enqueue_batch_sweep<TX>(dt, bp, Rc, B.SI, D, false, D.stream, s);
         if (rc) return rc;
       }
       HIP_OK(hipEventRecord(e1, s));
@@ -1617,7 +1655,7 @@ int batch_impl(smre_ctx* c, smre_dtype dt, int n, const smre_batch_image* im,
   rc = plan_batch(dt, n, im, bp, R, &B, true);
   if (rc) return rc;
   if (B.total > ws_bytes) return SMRE_ENOMEM;
-  rc = batch_setup<TX>(c, dt, n, im, bp, B, ws, host, &D, s);
+  rc = batch_setup<TX>(c, dt, n, im, bp, B, far, ws, host, &D, s);
   if (rc) return rc;
 
   int max_sw = 0;
@@ -1634,7 +1672,7 @@ int batch_impl(smre_ctx* c, smre_dtype dt, int n, const smre_batch_image* im,
     HIP_OK(hipGraphInstantiate(&gx[g], gr[g], nullptr, nullptr, 0));
     return SMRE_OK;
   };
-  bool stream = B.stream;
+  bool stream = D.stream;
   TimingAcc tacc;
   std::deque<std::pair<int, int>> inflight;
   int lag_slot = 0;

@@ -173,3 +173,33 @@ def test_a_short_solve_hands_on_that_its_image_streams(ctx, amp, streams):
     ws, _ = solved(ctx, amp * dense_corner(128, 128), list(range(1, 9)), tol=1e-12, max_sweeps=1,
                    region=16)
     assert int(signature_tail(ws)[0]) == streams
+
+
+@pytest.mark.parametrize("n,sides,amp,streams", [
+    (128, list(range(1, 9)), 1.0, True),       # 239 rounds a region
+    (33, [2, 3, 8], 1.0, True),                # fewer tiles than the sample holds
+    (128, list(range(1, 9)), 0.02, False),     # within the bounds
+    (128, list(range(1, 11)), 1.0, False),     # 420 rounds a region: visiting is as good
+])
+def test_a_dense_input_streams_from_the_first_sweep(ctx, n, sides, amp, streams):
+    ws, _ = solved(ctx, amp * dense_corner(n, n), sides, tol=0, max_sweeps=1, region=16)
+    # (a sweep that visits leaves every region's head word at 32 or at 0)
+    visited = int(heads(ws, n, n, 16, len(sides)).max()) > 0 or int(signature_tail(ws)[0]) == 0
+    assert visited != streams
+
+
+@pytest.mark.parametrize("use_graph", [True, False])
+@pytest.mark.parametrize("amps", [(1.0, 1.0, 1.0), (1.0, 0.05, 0.02), (0.1, 0.075, 1.0)])
+def test_dense_batch_equals_single(ctx, amps, use_graph):
+    # all images streaming, some, and some that go over to it while others are visited
+    sides = list(range(1, 9))
+    r2 = smre.chi2_bounds(sides)
+    xs0 = [a * dense_corner(n, n) for a, n in zip(amps, (70, 96, 48))]
+    xs = [x.clone() for x in xs0]
+    _, reps = ctx.project_batch(xs, sides, r2, tol=1e-4, max_sweeps=40, region=16,
+                                use_graph=use_graph)
+    for x0, x, rep in zip(xs0, xs, reps):
+        y = x0.clone()
+        _, one = ctx.project(y, sides, r2, tol=1e-4, max_sweeps=40, region=16)
+        assert torch.equal(x, y)
+        assert rep["sweeps"] == one["sweeps"] and rep["converged"] == one["converged"]
