@@ -780,11 +780,12 @@ __device__ __forceinline__ void write_rounds(int lane, SparseLds<TX, TQ, R, SMAX
 }
 
 // One region of one image, whole workgroup; false (nothing done) if the region is
-// to be streamed whole.  ready(): waits until the region's pixels may be read.
-template <typename TX, typename TQ, int R, int SMAX, bool KAHAN, typename Ready>
+// to be streamed whole.  ready(): waits until the region's pixels may be read;
+// loaded(): called by one wave that then has nothing left to do.
+template <typename TX, typename TQ, int R, int SMAX, bool KAHAN, typename Ready, typename Loaded>
 __device__ __forceinline__ bool sparse_job(const ImageDesc& a, int region, unsigned char* q,
                                            uint32_t* lv, SparseLds<TX, TQ, R, SMAX>& L,
-                                           bool shared, const Ready& ready) {
+                                           bool shared, const Ready& ready, const Loaded& loaded) {
   using SL = SparseLds<TX, TQ, R, SMAX>;
   constexpr int P = SL::SH::P, NW = SL::NW;
   const int r0 = region / a.nrx * R, c0 = (region - region / a.nrx * a.nrx) * R;
@@ -893,6 +894,7 @@ __device__ __forceinline__ bool sparse_job(const ImageDesc& a, int region, unsig
   if (wave == 1) {
     Loader<TX, TQ, R, SMAX, decltype(g)> ld{L, g, nw, a.H - r0, a.W - c0, lane, -64};
     ld.run();
+    loaded();
   } else {
     test_all<TX, TQ, R, SMAX>(L, wave / 2, lane, a.H - r0, a.W - c0, a.sides[0]);
     if (wave == 2) write_rounds<TX, TQ, R, SMAX>(lane, L, g);
@@ -1185,8 +1187,19 @@ __global__ __launch_bounds__(kPhaseThreads, sizeof(TX) == 4 && R <= 16 ? 3 : 2) 
     }
     const ImageDesc& a = *ap;
     const int64_t flag = img * p.flag_stride;
+    // The ticket of the next job, taken by the wave that loads when it has loaded
+    // all: in a job of many rounds near its end, else at once, so that the atomic's 2 us
+    // pass under the job.  (Taken at the start of every job it makes the workgroups that
+    // start first hold a second region of the first colour each while others already
+    // wait for it.  512 x 512, sides 1..8, us per sweep with every region streamed: 507,
+    // 335 now; every round taken for live: 1390, 775.  Taken after the job: 347, 780, and
+    // 5 to 10 us more a sweep of a quiet image.)
+    auto next = [&]() {
+      if (!items && (threadIdx.x & 63) == 0) ticket = atomicAdd(&p.ctrl->ticket[p.sweep & 1], 1);
+    };
     if (!items && it >= c4) {
       sweep_check<TX, R, kPhaseThreads>(p, a, it - c4, true);
+      if (threadIdx.x < 64) next();
     } else if (!items || !*(const int*)((const char*)p.done + flag)) {
       uint32_t* lv = (uint32_t*)(p.q + a.q_byte + a.live_off) +
                      (int64_t)region * (kLiveHead + a.nsides * live_words(R));
@@ -1202,7 +1215,8 @@ __global__ __launch_bounds__(kPhaseThreads, sizeof(TX) == 4 && R <= 16 ? 3 : 2) 
                              __HIP_MEMORY_SCOPE_AGENT);
       };
       int aborted, head;
-      if (!a.stream && sparse_job<TX, TQ, R, SMAX, KAHAN>(a, region, p.q, lv, L.sparse, shared, ready)) {
+      if (!a.stream && sparse_job<TX, TQ, R, SMAX, KAHAN>(a, region, p.q, lv, L.sparse, shared, ready,
+                                                      next)) {
         aborted = L.sparse.abort;
         head = L.sparse.head;
         if (shared) {
@@ -1217,6 +1231,7 @@ __global__ __launch_bounds__(kPhaseThreads, sizeof(TX) == 4 && R <= 16 ? 3 : 2) 
         if (threadIdx.x < 128)
           region_job<TX, TQ, R, SMAX, KAHAN>(a, region, p.q, L.dense, fresh(threadIdx.x & 63),
                                              shared, ready, ended);
+        if (threadIdx.x >= 64 && threadIdx.x < 128) next();
         __syncthreads();
         aborted = L.dense.ctr[2];
         if (threadIdx.x == 0) lv[0] = head;
@@ -1230,14 +1245,6 @@ __global__ __launch_bounds__(kPhaseThreads, sizeof(TX) == 4 && R <= 16 ? 3 : 2) 
     if (items) {
       it += gridDim.x;
     } else {
-      // (not before the job has ended, though that would hide the atomic's 2 us: the
-      // workgroups that start first would each hold a second region of the first
-      // colour while others already wait for it.  512 x 512, sides 1..8, us per
-      // sweep: all regions streamed 507 with the ticket taken at the job's start,
-      // 347 now; every round taken for live 1390, 780; a call of 60 sweeps on a quiet
-      // image 11.7 ms, 10.1)
-      if (threadIdx.x == 0) ticket = atomicAdd(&p.ctrl->ticket[p.sweep & 1], 1);
-      __syncthreads();
       it = __builtin_amdgcn_readfirstlane(ticket);
     }
   }
