@@ -682,7 +682,7 @@ int project_impl(smre_ctx* c, smre_dtype dt, void* x, int64_t H, int64_t W, int6
     if (stream && l.ncheck) launch_check<TX>(pl.R, l, s);
     // the host stays at most 2 kAhead sweeps ahead while there is something to look
     // for; sweeps queued past the last one find the flag and end at once
-    if ((checking || !stream) && sweep % kAhead == 0) {
+    if ((checking || !stream) && sweep % kAhead == 0 && sweep < p->max_sweeps) {
       const int e = sweep / kAhead % 2;
       if (sweep > kAhead) HIP_OK(hipEventSynchronize(c->lag_ev[1 - e]));
       const volatile int* seen = c->counters_host;
