@@ -687,9 +687,13 @@ int project_impl(smre_ctx* c, smre_dtype dt, void* x, int64_t H, int64_t W, int6
       if (sweep > kAhead) HIP_OK(hipEventSynchronize(c->lag_ev[1 - e]));
       const volatile int* seen = c->counters_host;
       if (seen[0]) break;
-      // many regions stream: the leaner kernel is faster at that, and what it
-      // leaves out (the live bits) is not needed again in this problem (256 x 256
-      // grey levels, 3 x 40 sweeps: 40 against 55 ms)
+      // Many regions stream: the leaner kernel is faster at that, for good, as it
+      // leaves out the live bits.  Sides 1..8, share of streaming regions, us per
+      // sweep in one launch and by stream_phase: 512 x 512, 0.05: 339 and 321, 0.35:
+      // 349 and 326; 1024 x 1024, 0.08: 380 and 395, 0.34: 412 and 393, 0.65: 443 and
+      // 391; 2048 x 2048, 0.3: 850 and 1590.  (The line is not drawn lower for small
+      // images: they gain 7% and stand to lose the sparse sweeps, which a quiet image
+      // takes 39 us for.)
       if (!stream && 3 * (int64_t)seen[1] > nreg) stream = true;
       HIP_OK(hipEventRecord(c->lag_ev[e], s));
     }

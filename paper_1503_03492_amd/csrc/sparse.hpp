@@ -21,9 +21,12 @@
 // is the one of the full visit, bit for bit (but for the sign of zeros).
 //
 // The test may say "might exceed" of a window that does not (the visit then
-// changes nothing), never the reverse: it adds at most 2 S FP32 squares, all
-// positive, a relative error below 4e-6 for S <= 32, as is that of the FP32
-// sums of run_side, and compares with r2 (1 - kTestMargin), kTestMargin = 2e-5.
+// changes nothing), never the reverse.  It compares an FP32 sum with
+// r2 (1 - kTestMargin).  All terms are positive, so a sum is within its longest chain
+// of roundings of the exact one: test_all carries one sum through all sides (S (S + 3) / 2
+// roundings up to side S, 560 at side 32, 3.4e-5), window_test adds 2 S values; a visit's
+// own FP32 sum comes on top (below 50 roundings).  A static_assert ties the margin to
+// that.
 //
 // Workgroup = 3 waves: wave 0 (consumer) tests and projects; wave 1 (loader)
 // walks the live rounds in visiting order ahead of it and puts their increments
@@ -33,15 +36,17 @@
 // on through LDS counters; every wait is bounded, as in region_job.
 //
 // A side more than half of whose rounds are live is visited round by round
-// without tests (a test costs about as much as a visit).  A visit takes 1300 to
-// 2000 cycles (0.6 to 0.9 us), a round of region_job, which streams whole pages,
-// 0.38 us; so a region more than about a quarter of whose rounds are live goes
-// through region_job for kDenseSweeps sweeps, after which a sweep that takes every
-// round for live finds the live ones again.
+// without tests (a test costs about as much as a visit).  A region more than about a
+// quarter of whose rounds are live goes through region_job, which streams whole pages,
+// for kDenseSweeps - 1 sweeps, after which a sweep that takes every round for live finds
+// the live ones again.  us per sweep of 512 x 512 noise, visited and streamed: sides
+// 1..8, share of live rounds 0.14: 260 and 350, 0.25: 376 and 350, 0.34: 432 and 350;
+// BF16 increments 0.25: 385 and 376; FP64 0.25: 428 and 445; region side 8 0.22: 338
+// and 338.
 //
-// Measured, us per sweep with its check, start of this design against now: 512 x 512
-// sides 1..8, 338 against 174 (331 in the first sweep, 156 in the last of 120);
-// 1024 x 1024 sides 1..16, 2550 against 301 (1340, 238).  What bounds it: the chain
+// Measured, us per sweep with its check, a full visit against this: 512 x 512
+// sides 1..8, 338 against 158 (264 in the first sweep, 133 in the last of 120);
+// 1024 x 1024 sides 1..16, 2550 against 250 (1142, 183).  What bounds it: the chain
 // of visits of the slowest region, and instruction fetch (the code of a side, about
 // 4 KB, runs for a few rounds per job).
 #pragma once
@@ -53,10 +58,15 @@ namespace smre {
 
 constexpr int kPhaseThreads = 192;  // consumer, loader, writer
 constexpr float kTestMargin = 1e-4f;
+// Roundings between a sum of the test and the sum a visit decides by: test_all's chain,
+// a pixel's conversion from FP64 (twice in its square), the product r2 (1 - margin), and
+// the visit's own chain.
+constexpr int kTestRoundings = 32 * (32 + 3) / 2 + 2 + 3 + 50;
+static_assert(kTestRoundings * (1.0 / (1 << 24)) < 0.5 * kTestMargin, "the test's margin");
 // A wait here lasts while the consumer tests and visits rounds that need nothing
 // from the ring (a region of side 32 has up to 32768 rounds): ~1 s of sleeps.
 constexpr int kSparseSpin = 1 << 24;
-constexpr int kDenseSweeps = 32;
+constexpr int kDenseSweeps = 32;  // head word of a region that goes over to streaming
 
 // Live bits of a region in HBM: kLiveHead words (word 0: 0 = sparse, 1 = sparse
 // with every round taken for live, h > 1 = page streaming for h - 1 sweeps more),
@@ -163,17 +173,16 @@ template <typename TX, typename TQ, int R, int SMAX> struct SparseLds {
   static constexpr int NWM = R * R / 64;  // window masks per side
   // a slot holds the largest round, read by all lanes, and the 0..3 bytes by
   // which a round may start off a 4-byte boundary
-  static constexpr int max_elem(bool lanes) {
+  static constexpr int max_elem() {
     int m = 0;
     for (int s = 1; s <= SMAX; ++s) {
       const Pattern p = pattern(R, s);
-      const int e = p.br * p.bc * s * s + (lanes ? p.gr * p.gc : 0);
+      const int e = p.br * p.bc * s * s + p.gr * p.gc;
       if (e > m) m = e;
     }
     return m;
   }
-  static constexpr int MAXB = max_elem(false) * ES;
-  static constexpr int SLOT = (max_elem(true) * ES + 4 + 15) / 16 * 16;
+  static constexpr int SLOT = (max_elem() * ES + 4 + 15) / 16 * 16;
   static constexpr int NIN = SLOT <= 4096 ? 5 : SLOT <= 8192 ? 4 : 2;
   static constexpr int NOUT = SLOT <= 4096 ? 2 : SLOT <= 8192 ? 2 : 1;
   static constexpr int ODUMMY = NOUT * SLOT;  // targets of masked lanes' writes
@@ -1004,8 +1013,8 @@ struct PhaseArgs {
                        // sweep before
 };
 
-// Waits, with one wave, until the regions of a (2 n + 1)^2 neighbourhood that
-// `needs` names have ended the sweep.
+// Waits, with one wave, until those of a region and the eight around it that `needs`
+// names have ended the sweep.
 template <typename Needs>
 __device__ __forceinline__ void wait_regions(const PhaseArgs& p, const ImageDesc& a, int ry, int rx,
                                              const Needs& needs) {
