@@ -2,13 +2,13 @@
 //
 // Full Dykstra (Sec. 2.3, Algorithm 2, projection Eq. (dykstra:if)) runs as
 // "region phases": the anchor plane (top-left pixels of windows) is cut into
-// R x R regions, coloured 2 (p mod 2) + (q mod 2).  One launch processes all
-// regions of one colour; with R >= smax - 1 their pixel footprints
-// (R + smax - 1)^2 are disjoint, so the launch needs no ordering between
-// workgroups.  Inside a region the workgroup visits every window anchored in
-// it: side by side (descending), then tiling offset (a', b') relative to the
-// region origin in raster order; the windows of one offset are disjoint
-// (Sec. 2.3), so a step projects all of them at once.
+// R x R regions, coloured 2 (p mod 2) + (q mod 2).  With R >= smax - 1 the pixel
+// footprints (R + smax - 1)^2 of one colour's regions are disjoint, so they need no
+// ordering between them.  This file holds a region's visit of all its windows; which
+// regions get one, and the kernels, are in sparse.hpp.  Inside a region the workgroup
+// visits every window anchored in it: side by side (descending), then tiling offset
+// (a', b') relative to the region origin in raster order; the windows of one offset
+// are disjoint (Sec. 2.3), so a step projects all of them at once.
 //
 // Workgroup = 2 waves:
 //   wave 0 (consumer) keeps the region's x footprint in LDS for the whole
@@ -404,8 +404,8 @@ struct RoundEntry {
 // enumeration the oracle's region order uses.
 __host__ __device__ constexpr int round_table_len(int R) { return R * R + 2; }
 
-// Everything a region job needs about its image.  Passed by value for a
-// single image; an array in device memory for a batch.
+// Everything a region job needs about its image: in device memory, one or an array
+// of them (stream_phase takes it by value).
 struct ImageDesc {
   void* x;                 // image (TX), row stride ld
   const RegionStream* rs;  // page layout of each region's increments

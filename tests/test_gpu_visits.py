@@ -2,10 +2,13 @@
 change something, every round taken for live, whole pages streamed inside the
 one-launch sweep, and the kernel that only streams.  A warm solve is made to take
 one of them through the words its workspace holds (the head word of each region's
-live bits, the last word of the signature)."""
+live bits, the last word of the signature).  And: which solves, warm starts and batches
+stream."""
+import numpy as np
 import pytest
 import torch
 
+import oracle
 import paper_1503_03492_amd as smre
 
 pytestmark = pytest.mark.gpu
@@ -203,3 +206,29 @@ def test_dense_batch_equals_single(ctx, amps, use_graph):
         _, one = ctx.project(y, sides, r2, tol=1e-4, max_sweeps=40, region=16)
         assert torch.equal(x, y)
         assert rep["sweeps"] == one["sweeps"] and rep["converged"] == one["converged"]
+
+
+@pytest.mark.parametrize("amp,streams", [(4.0, 1), (0.6, 0)])
+def test_warm_start_after_either_kind_of_solve(ctx, amp, streams):
+    # eight sweeps that go over to streaming on the way (half of the image dense), or
+    # stay with visiting, then a warm solve of a moved image from the increments they leave
+    H, W, sides, R = 70, 61, list(range(1, 9)), 16
+    r2 = smre.chi2_bounds(sides)
+    rng = np.random.default_rng(8)
+    xa = amp * rng.standard_normal((H, W))
+    xa[:, 32:] *= 0.1
+    xa[20:24, 40:44] += 3.0
+    xb = xa + 0.05 * rng.standard_normal((H, W))
+    o = smre.ProjectOptions(tol=0, max_sweeps=8, region=R)
+    ws = torch.zeros(ctx.workspace_size(smre.F64, H, W, sides, r2, o), dtype=torch.uint8,
+                     device="cuda")
+    ctx.project(torch.from_numpy(xa).cuda(), sides, r2, o, workspace=ws)
+    assert int(signature_tail(ws)[0]) == streams
+    x = torch.from_numpy(xb).cuda()
+    ctx.project(x, sides, r2, tol=0, max_sweeps=3, region=R, warm=True, workspace=ws)
+    _, _, _, ia = oracle.dykstra(xa, sides, r2, tol=0, max_sweeps=8, order=oracle.ORDER_REGION,
+                                 region=R, want_incs=True)
+    ref, _, _ = oracle.dykstra(xb, sides, r2, tol=0, max_sweeps=3, order=oracle.ORDER_REGION,
+                               region=R, incs0=ia)
+    # a few hundred roundings of 1e-16 a sweep
+    assert np.max(np.abs(x.cpu().numpy() - ref)) <= 1e-11 * np.max(np.abs(ref))
