@@ -416,13 +416,6 @@ int launch_phase_any(smre_dtype dt, int inc, int kahan, int R, int SI, int grid,
                : launch_phase_r<float, float, false>(R, SI, grid, p, st, sb, s);
 }
 
-template <typename TX> void launch_check(int R, const PhaseArgs& p, hipStream_t s) {
-  const dim3 grid(p.ncheck), block(256);
-  if (R == 8) hipLaunchKernelGGL((sweep_check_kernel<TX, 8>), grid, block, 0, s, p);
-  else if (R == 16) hipLaunchKernelGGL((sweep_check_kernel<TX, 16>), grid, block, 0, s, p);
-  else hipLaunchKernelGGL((sweep_check_kernel<TX, 32>), grid, block, 0, s, p);
-}
-
 // Few rounds in a region: streaming its increments whole costs less than finding
 // out what may be left out (64 x 64 FP64, sides 1, 2, 4, 24 rounds: 11.1 against
 // 15.6 ms for 200 sweeps; 219 x 536, sides 1, 2, 4, 8, 88 rounds: 4.5 against 5.2 ms
@@ -666,7 +659,9 @@ int project_impl(smre_ctx* c, smre_dtype dt, void* x, int64_t H, int64_t W, int6
     l.streams = &c->ctrl->streams[sweep & 1];
     l.decide = checked(sweep);
     // (the sweep before a checked one keeps the image)
-    l.ncheck = l.decide || (sweep < p->max_sweeps && checked(sweep + 1)) ? l.nregions[0] : 0;
+    l.ncheck = 0;
+    if (l.decide || (sweep < p->max_sweeps && checked(sweep + 1)))
+      l.ncheck = stream ? (int)std::min<int64_t>(kCheckBlocks, check_tiles(H, W)) : l.nregions[0];
     for (int color = 0; color < (stream ? 4 : 1); ++color) {
       StreamLaunch st{a, color >> 1, color & 1, (pl.nrx - (color & 1) + 1) / 2};
       const int jobs = stream ? l.nregions[color] : grid;
@@ -679,7 +674,8 @@ int project_impl(smre_ctx* c, smre_dtype dt, void* x, int64_t H, int64_t W, int6
       rc = timing_end(c, tacc, s, slot);
       if (rc) return rc;
     }
-    if (stream && l.ncheck) launch_check<TX>(pl.R, l, s);
+    if (stream && l.ncheck)
+      hipLaunchKernelGGL((sweep_check_kernel<TX>), dim3(l.ncheck), dim3(256), 0, s, l);
     // the host stays at most 2 kAhead sweeps ahead while there is something to look
     // for; sweeps queued past the last one find the flag and end at once
     if ((checking || !stream) && sweep % kAhead == 0 && sweep < p->max_sweeps) {

@@ -1032,26 +1032,22 @@ __device__ __forceinline__ void wait_regions(const PhaseArgs& p, const ImageDesc
   if (lane == 0) atomicOr(p.abort, 1);
 }
 
-// Check job b of a sweep: the pixels of 2 x 2 regions are compared with (and kept
-// for) the sweep before; the last job to end decides.
-template <typename TX, int R, int NT>
-__device__ __forceinline__ void sweep_check(const PhaseArgs& p, const ImageDesc& a, int b,
-                                            bool shared) {
-  const int tid = fresh(threadIdx.x);
-  const int nbx = (a.nrx + 1) / 2, by = b / nbx, bx = b - b / nbx * nbx;
-  if (shared && tid < 64) wait_regions(p, a, 2 * by, 2 * bx, [](int, int) { return true; });
-  __syncthreads();
-  const int h = min(2 * R, a.H - 2 * by * R), w = min(2 * R, a.W - 2 * bx * R);
-  const TX* x = (const TX*)a.x + (int64_t)2 * by * R * a.ld + 2 * bx * R;
-  TX* prev = (TX*)p.prev + (int64_t)2 * by * R * a.W + 2 * bx * R;
-  constexpr int NB = (4 * R * R + NT - 1) / NT;
+// The pixels of a tile of TH x TW at (y0, x0), compared with (and kept for) the sweep
+// before: a thread's largest change.
+template <typename TX, int TH, int TW, int NT>
+__device__ __forceinline__ double check_tile(const PhaseArgs& p, const ImageDesc& a, int y0, int x0,
+                                             int tid, bool shared) {
+  const int h = min(TH, a.H - y0), w = min(TW, a.W - x0);
+  const TX* x = (const TX*)a.x + (int64_t)y0 * a.ld + x0;
+  TX* prev = (TX*)p.prev + (int64_t)y0 * a.W + x0;
+  constexpr int NB = (TH * TW + NT - 1) / NT;
   constexpr int NU = NB < 4 ? NB : 4;
   double d = 0.0;
-  for (int i0 = tid; i0 < 4 * R * R; i0 += NU * NT) {
+  for (int i0 = tid; i0 < TH * TW; i0 += NU * NT) {
     TX v[NU], o[NU];
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
-      const int i = i0 + u * NT, r = i / (2 * R), c = i % (2 * R);
+      const int i = i0 + u * NT, r = i / TW, c = i % TW;
       v[u] = o[u] = TX(0);
       if (r < h && c < w) {
         v[u] = load_pixel(x + (int64_t)r * a.ld + c, shared);
@@ -1060,12 +1056,17 @@ __device__ __forceinline__ void sweep_check(const PhaseArgs& p, const ImageDesc&
     }
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
-      const int i = i0 + u * NT, r = i / (2 * R), c = i % (2 * R);
+      const int i = i0 + u * NT, r = i / TW, c = i % TW;
       if (r < h && c < w) prev[(int64_t)r * a.W + c] = v[u];
       d = fmax(d, fabs((double)v[u] - (double)o[u]));
     }
   }
-  if (!p.decide) return;
+  return d;
+}
+
+// The last of a sweep's p.ncheck workgroups to come here with its largest change
+// decides.
+template <int NT> __device__ __forceinline__ void check_decide(const PhaseArgs& p, double d, int tid) {
   __shared__ double part[NT / 64];
   for (int o = 32; o > 0; o >>= 1) d = fmax(d, __shfl_xor(d, o));
   if ((tid & 63) == 0) part[tid >> 6] = d;
@@ -1094,11 +1095,35 @@ __device__ __forceinline__ void sweep_check(const PhaseArgs& p, const ImageDesc&
   }
 }
 
-// The check jobs alone, one per workgroup (after launches of stream_phase).
-template <typename TX, int R>
-__global__ __launch_bounds__(256) void sweep_check_kernel(PhaseArgs p) {
+// Check job b of a sweep in one launch: the pixels of 2 x 2 regions.
+template <typename TX, int R, int NT>
+__device__ __forceinline__ void sweep_check(const PhaseArgs& p, const ImageDesc& a, int b) {
+  const int tid = fresh(threadIdx.x);
+  const int nbx = (a.nrx + 1) / 2, by = b / nbx, bx = b - b / nbx * nbx;
+  if (tid < 64) wait_regions(p, a, 2 * by, 2 * bx, [](int, int) { return true; });
+  __syncthreads();
+  const double d = check_tile<TX, 2 * R, 2 * R, NT>(p, a, 2 * by * R, 2 * bx * R, tid, true);
+  if (p.decide) check_decide<NT>(p, d, tid);
+}
+
+// The check of a sweep after launches of stream_phase: tiles of whole 128-pixel rows,
+// by at most kCheckBlocks workgroups, since each adds to one counter.  (With a
+// workgroup per 2 x 2 regions 2048 x 2048 pixels took 80 us, 209 with region side 8;
+// 29 now.)
+constexpr int kCheckBlocks = 1024, kCheckH = 8, kCheckW = 128;
+__host__ __device__ __forceinline__ int64_t check_tiles(int64_t H, int64_t W) {
+  return ((H + kCheckH - 1) / kCheckH) * ((W + kCheckW - 1) / kCheckW);
+}
+template <typename TX> __global__ __launch_bounds__(256) void sweep_check_kernel(PhaseArgs p) {
   if (*p.done) return;
-  sweep_check<TX, R, 256>(p, *p.imgs, blockIdx.x, false);
+  const ImageDesc& a = *p.imgs;
+  const int64_t n = check_tiles(a.H, a.W);
+  const int nx = (a.W + kCheckW - 1) / kCheckW;
+  double d = 0.0;
+  for (int64_t t = blockIdx.x; t < n; t += gridDim.x)
+    d = fmax(d, check_tile<TX, kCheckH, kCheckW, 256>(p, a, (int)(t / nx) * kCheckH,
+                                                      (int)(t % nx) * kCheckW, threadIdx.x, false));
+  if (p.decide) check_decide<256>(p, d, threadIdx.x);
 }
 
 // One image, one colour, every region through region_job: block b takes the b-th
@@ -1207,7 +1232,7 @@ __global__ __launch_bounds__(kPhaseThreads, sizeof(TX) == 4 && R <= 16 ? 3 : 2) 
       if (!items && (threadIdx.x & 63) == 0) ticket = atomicAdd(&p.ctrl->ticket[p.sweep & 1], 1);
     };
     if (!items && it >= c4) {
-      sweep_check<TX, R, kPhaseThreads>(p, a, it - c4, true);
+      sweep_check<TX, R, kPhaseThreads>(p, a, it - c4);
       if (threadIdx.x < 64) next();
     } else if (!items || !*(const int*)((const char*)p.done + flag)) {
       uint32_t* lv = (uint32_t*)(p.q + a.q_byte + a.live_off) +

@@ -232,3 +232,20 @@ def test_warm_start_after_either_kind_of_solve(ctx, amp, streams):
                                region=R, incs0=ia)
     # a few hundred roundings of 1e-16 a sweep
     assert np.max(np.abs(x.cpu().numpy() - ref)) <= 1e-11 * np.max(np.abs(ref))
+
+
+@pytest.mark.parametrize("H,W", [(1100, 1070), (3000, 41), (7, 5000)])
+@pytest.mark.parametrize("every", [1, 2])
+def test_the_streaming_solve_reports_its_largest_change(ctx, H, W, every):
+    # (more tiles than the check has workgroups, and images narrower than a tile)
+    sides, r2 = [1, 2, 4], smre.chi2_bounds([1, 2, 4])
+    x0 = dense_corner(max(H, W), min(H, W))[:H, :W].contiguous() if H * W < 10 ** 6 else \
+        3.0 * torch.randn(H, W, generator=torch.Generator().manual_seed(6)).cuda()
+    xs = []
+    for sweeps in (3, 4):
+        xs.append(x0.clone())
+        ctx.project(xs[-1], sides, r2, tol=0, max_sweeps=sweeps, region=16)
+    x = x0.clone()
+    _, rep = ctx.project(x, sides, r2, tol=1e-12, max_sweeps=4, check_every=every, region=16)
+    assert torch.equal(x, xs[1])
+    assert rep["last_delta"] == float((xs[1].double() - xs[0].double()).abs().max())
