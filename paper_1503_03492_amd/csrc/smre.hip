@@ -661,7 +661,7 @@ int project_impl(smre_ctx* c, smre_dtype dt, void* x, int64_t H, int64_t W, int6
     // (the sweep before a checked one keeps the image)
     l.ncheck = 0;
     if (l.decide || (sweep < p->max_sweeps && checked(sweep + 1)))
-      l.ncheck = stream ? (int)std::min<int64_t>(kCheckBlocks, check_tiles(H, W)) : l.nregions[0];
+      l.ncheck = stream ? std::min(kCheckBlocks, check_tiles((int)H, (int)W)) : l.nregions[0];
     for (int color = 0; color < (stream ? 4 : 1); ++color) {
       StreamLaunch st{a, color >> 1, color & 1, (pl.nrx - (color & 1) + 1) / 2};
       const int jobs = stream ? l.nregions[color] : grid;

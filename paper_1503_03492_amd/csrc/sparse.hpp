@@ -1106,23 +1106,22 @@ __device__ __forceinline__ void sweep_check(const PhaseArgs& p, const ImageDesc&
   if (p.decide) check_decide<NT>(p, d, tid);
 }
 
-// The check of a sweep after launches of stream_phase: tiles of whole 128-pixel rows,
+// The check of a sweep after launches of stream_phase: tiles of 64-pixel rows,
 // by at most kCheckBlocks workgroups, since each adds to one counter.  (With a
 // workgroup per 2 x 2 regions 2048 x 2048 pixels took 80 us, 209 with region side 8;
 // 29 now.)
-constexpr int kCheckBlocks = 1024, kCheckH = 8, kCheckW = 128;
-__host__ __device__ __forceinline__ int64_t check_tiles(int64_t H, int64_t W) {
+constexpr int kCheckBlocks = 1024, kCheckH = 16, kCheckW = 64;
+__host__ __device__ __forceinline__ int check_tiles(int H, int W) {
   return ((H + kCheckH - 1) / kCheckH) * ((W + kCheckW - 1) / kCheckW);
 }
 template <typename TX> __global__ __launch_bounds__(256) void sweep_check_kernel(PhaseArgs p) {
   if (*p.done) return;
   const ImageDesc& a = *p.imgs;
-  const int64_t n = check_tiles(a.H, a.W);
-  const int nx = (a.W + kCheckW - 1) / kCheckW;
+  const int n = check_tiles(a.H, a.W), nx = (a.W + kCheckW - 1) / kCheckW;
   double d = 0.0;
-  for (int64_t t = blockIdx.x; t < n; t += gridDim.x)
-    d = fmax(d, check_tile<TX, kCheckH, kCheckW, 256>(p, a, (int)(t / nx) * kCheckH,
-                                                      (int)(t % nx) * kCheckW, threadIdx.x, false));
+  for (int t = blockIdx.x; t < n; t += gridDim.x)
+    d = fmax(d, check_tile<TX, kCheckH, kCheckW, 256>(p, a, t / nx * kCheckH, t % nx * kCheckW,
+                                                      threadIdx.x, false));
   if (p.decide) check_decide<256>(p, d, threadIdx.x);
 }
 
