@@ -79,7 +79,8 @@ __global__ __launch_bounds__(256) void nonfinite_kernel(const TX* x, int64_t ld,
 // The input of a full Dykstra solve: the same test, and, by the first `tiles` blocks,
 // how many windows are far over their bound, in up to kFarTiles tiles of 16 x 16
 // anchors spread over the image: enough to tell a solve that will stream
-// (starts_streaming in smre.hip).
+// (starts_streaming in smre.hip).  Bound by latency; the tiles come first, as their
+// blocks take longest (512 x 512, sides 1..8: 8 us for the launch, 5 without tiles).
 constexpr int kFarTiles = 64;
 struct FarTest {
   int tiles, smax;
